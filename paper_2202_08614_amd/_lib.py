@@ -539,7 +539,7 @@ def quantize(tree: DeviceTree, dtype: int) -> DeviceTree:
         raise ValueError("quantize needs an F32 tree")
     dev = tree.coeffs.device
     lay = tree.layout
-    q = torch.zeros((tree.leaf_stride, layout_record_words(lay.n_sigma, lay.n_sh_fourier, dtype), 4),
+    q = torch.empty((tree.leaf_stride, layout_record_words(lay.n_sigma, lay.n_sh_fourier, dtype), 4),
                     dtype=torch.int32, device=dev)
     scale = torch.empty((tree.leaf_stride,), dtype=torch.float32, device=dev)
     _check(lib().fpo_quantize(_t_ptr(tree.coeffs), tree.n_leaves, tree.leaf_stride, ctypes.byref(lay), int(dtype),

@@ -576,9 +576,14 @@ constexpr int64_t kWaveRayBatch = 32768;
 // fixed order.  All lanes hold the same bits, branches on the result stay
 // uniform, and no step goes through LDS.
 template <int CTRL>
+__device__ inline float dpp_move(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
 __device__ inline float dpp_add(float v)
 {
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+    return v + dpp_move<CTRL>(v);
 }
 __device__ inline float wave_sum(float v)
 {

@@ -63,6 +63,38 @@ def test_quantize_bit_exact(dev, dtype, kind):
     assert np.all(qt.scale.cpu().numpy()[len(dijk):] == 1.0)
 
 
+@pytest.mark.parametrize("dtype,kind", [(_lib.FPO_BF16, "bf16"), (_lib.FPO_FP8_E4M3, "fp8")])
+@pytest.mark.parametrize("n,stride", [(1, 1), (15, 15), (17, 20), (4099, 4100)])
+def test_quantize_edges(dev, dtype, kind, n, stride):
+    """Whole range of magnitudes (scales from subnormal to 2^120, where the
+    quotient takes the full division), values near the rounding points, signed
+    zeros; leaf counts around the 16 leaves of a block.  Equal bit for bit."""
+    import torch
+    rng = np.random.default_rng(n)
+    k = rng.standard_normal((n, 166)).astype(np.float32)
+    k *= np.float32(2.0) ** rng.integers(-14, 3, (n, 166)).astype(np.float32)
+    k *= np.float32(2.0) ** rng.choice([0, 0, 0, -70, -126, 59, 61, 110], (n, 1)).astype(np.float32)
+    k[rng.random((n, 166)) < 0.05] = -0.0
+    k[n // 2, :] = -0.0
+    src = torch.from_numpy(k).to(dev)
+    perm = np.arange(n)
+    layout = _lib.make_layout(60.0, 64.0)
+    recs = torch.empty((stride, 48, 4), dtype=torch.float32, device=dev)
+    _lib.pack_coeffs(src, torch.from_numpy(perm).to(dev), n, stride, recs, layout)
+    tree = _lib.DeviceTree(torch.zeros((1, 8), dtype=torch.int32, device=dev), 1, 1, recs, None, _lib.FPO_F32, n,
+                           stride, perm, layout)
+    note(f"fpo_quantize {kind} edges n={n}")
+    qt = _lib.quantize(tree, dtype)
+    torch.cuda.synchronize()
+    want_codes, want_scale = codec.quantize(k, kind)
+    assert np.array_equal(qt.scale.cpu().numpy()[:n].view(np.uint32), want_scale.view(np.uint32))
+    raw = qt.coeffs.cpu().numpy()
+    got = _codes_from_records(raw, dtype, perm, n)
+    assert np.array_equal(got, want_codes), np.argwhere(got != want_codes)[:5]
+    assert not raw.reshape(stride, -1)[n:].any()
+    assert np.all(qt.scale.cpu().numpy()[n:] == 1.0)
+
+
 @pytest.mark.parametrize("dtype,kind,min_db", [(_lib.FPO_BF16, "bf16", 50.0), (_lib.FPO_FP8_E4M3, "fp8", 25.0)])
 def test_quantised_render_c1(oracle_lib, dev, dtype, kind, min_db):
     """Kernel error: GPU render of the quantised store against the oracle on
