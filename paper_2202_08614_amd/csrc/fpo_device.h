@@ -233,8 +233,15 @@ struct NoStop {
 
 // TWO: descend through the two-level table where the tree has one (the
 // snapshot camera renders; elsewhere the extra registers cost occupancy).
-template <bool TWO = false, int STRIDE = kBlock, class Visitor, class Stop>
-__device__ inline void walk(const TreeDev& T, const Ray& r, int* stk, Visitor& vis, float t_end, Stop& stop)
+// PART: report only the segments whose entry lies in [t_start, t_end).  The
+// walk starts by descending to the slot around t_start and takes that slot's
+// own entry time (the last of its lower planes) as t_cur.  Every entry time is
+// then a plane's crossing time by the same expression (p - x) k as in a walk
+// from 0, so that of the parts of a chord exactly one reports each segment,
+// also where the descent at t_start rounds into a neighbouring slot.
+template <bool TWO = false, int STRIDE = kBlock, bool PART = false, class Visitor, class Stop>
+__device__ inline void walk(const TreeDev& T, const Ray& r, int* stk, Visitor& vis, float t_end, Stop& stop,
+                            float t_start = 0.0f)
 {
     // The child table is read through a buffer resource: 32-bit byte offsets
     // (no 64-bit address arithmetic per step), and a read past the table
@@ -262,7 +269,7 @@ __device__ inline void walk(const TreeDev& T, const Ray& r, int* stk, Visitor& v
     // corner pos (mirrored lattice, exact in FP32), edge 2^csh; each stacked
     // entry is kept under the edge exponent of its child slot
     int csh = D - 1;
-    float t_cur = 0.0f;
+    float t_cur = PART ? t_start : 0.0f;
     float pos[3];
     int no = 0;
     {
@@ -323,6 +330,11 @@ __device__ inline void walk(const TreeDev& T, const Ray& r, int* stk, Visitor& v
         }
         if (ch > 0) ch = 0;   // malformed table or past the deepest level: treat as empty
         const float sz = __builtin_ldexpf(1.0f, csh);
+        if constexpr (PART) {
+            if (it == 0 && t_start > 0.0f)
+                t_cur = fmaxf(fmaxf((pos[0] - xf[0]) * k[0], (pos[1] - xf[1]) * k[1]),
+                              fmaxf((pos[2] - xf[2]) * k[2], 0.0f));
+        }
         float te[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) te[a] = (pos[a] + sz - xf[a]) * k[a];
@@ -353,7 +365,7 @@ __device__ inline void walk(const TreeDev& T, const Ray& r, int* stk, Visitor& v
             }
             ch_next = __builtin_amdgcn_raw_buffer_load_b32(ct, no * 4, 0, 0);
         }
-        if (ch < 0) {
+        if (ch < 0 && (!PART || t_cur >= t_start)) {
             const int leaf = -ch - 1;
             if (leaf < T.n_leaves && vis.segment(leaf, t_cur, t_exit)) return;
         }

@@ -3,9 +3,9 @@
 //
 // Work mapping for camera renders: one wave64 renders an 8x8 pixel tile, a
 // 256-thread block a 16x16 tile.  Blocks are dispatched round-robin over the
-// 8 XCDs of the MI355X (each with its own L2); the block-to-tile map hands
-// each XCD a contiguous band of tiles so that neighbouring rays, which cross
-// the same leaves, share one L2.
+// 8 XCDs of the MI355X (each with its own L2); the block-to-tile map hands the
+// XCDs whole rows of tiles in turn (xcd_row), the skip pre-pass a contiguous
+// band each.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,8 +30,12 @@ constexpr int kCamsPerLaunch = 16;
 // 2.4% (1.9% with two launches in flight) per launch; the snapshot kernel
 // (64 VGPRs) was 1.9% slower so.
 constexpr int cam_waves(int mode) { return mode >= 16 ? 4 : 1; }
-constexpr int cam_tile_w(int waves) { return waves >= 2 ? 16 : 8; }
-constexpr int cam_tile_h(int waves) { return waves >= 4 ? 16 : 8; }
+// A wave of `parts` lanes per ray (render_cam_kernel) takes 64 / parts pixels:
+// 8x8, 8x4, 4x4, 4x2 or 2x2.
+constexpr int wave_tile_w(int parts) { return parts <= 2 ? 8 : parts <= 8 ? 4 : 2; }
+constexpr int wave_tile_h(int parts) { return 64 / parts / wave_tile_w(parts); }
+constexpr int cam_tile_w(int waves, int parts) { return (waves >= 2 ? 2 : 1) * wave_tile_w(parts); }
+constexpr int cam_tile_h(int waves, int parts) { return (waves >= 4 ? 2 : 1) * wave_tile_h(parts); }
 
 struct CamDev {
     float frame[12];                 // eye, forward, right * tan_x, up * tan_y
@@ -47,7 +51,8 @@ struct CamLaunch {
     const float2* skip;              // skip modes: [n_cams][H][W] (t_start, t_end) from the cube entry
     const uint32_t* bits;            // coarse occupancy (suffix checks)
     int32_t W, H, bx_per_cam, blocks_per_cam, n_cams;
-    int32_t cbx_per_cam, cblocks_per_cam;   // camera kernel tiles (cam_tile_w x cam_tile_h of the mode)
+    int32_t cbx_per_cam, crows_per_cam;     // camera kernel tiles (cam_tile_w x cam_tile_h of the mode)
+    int32_t group_rows;              // tile rows per XCD group (xcd_row)
     uint32_t snap_bytes;             // BUF kernels: bytes of one camera's snapshot records
     float bg[3];
     float stop_T;
@@ -70,6 +75,19 @@ __device__ inline int xcd_band(int bid, int nblocks)
 {
     const int per = nblocks >> 3;
     return (bid & 7) * per + (bid >> 3);
+}
+
+// Camera kernels: block index -> tile row of the launch (the rows of all
+// cameras, one camera after another) and column bx.  The rows go out in groups
+// of group_rows, eight groups at a time, one per XCD; the XCDs' order turns by
+// one from one eight to the next.  render_impl chooses the group.
+__device__ inline int xcd_row(int bid, int bx_per_row, int group_rows, int& bx)
+{
+    const int j = bid >> 3;
+    const int r = j / bx_per_row;            // row among this XCD's rows
+    bx = j - r * bx_per_row;
+    const int k = r / group_rows;
+    return (8 * k + (((bid & 7) + k) & 7)) * group_rows + (r - k * group_rows);
 }
 
 // Skip pre-pass: per pixel, a part of the chord [t_start, t_end] outside
@@ -190,26 +208,40 @@ __global__ __launch_bounds__(kBlock) void skip_scan_kernel(SkipLaunch a)
 // SKIP: walk only the proven part [t_start, t_end] of each chord that the
 // skip pre-pass left in a.skip.  BUF (snapshot modes, records within 4 GiB):
 // snapshot reads through a buffer resource, and at most 64 VGPRs.
-template <int MODE, bool SKIP, int N1 = FPO_N_SIGMA, int N2 = FPO_N_SH_FOURIER, bool BUF = false,
+//
+// PARTS > 1: that many lanes share a ray, each walking an equal part of its
+// chord from transmittance 1; the parts' colours and transmittances are then
+// composed front to back, C = C_0 + T_0 (C_1 + T_1 (...)).  A launch of few
+// waves lasts as long as its longest rays (each step waits for two or three
+// dependent reads, about 2 us), and this cuts them.  The stop rule stays the
+// walk's: the part in which the ray's transmittance falls below stop_T is
+// walked again from the transmittance it is entered with, the later ones are
+// dropped.
+template <int MODE, bool SKIP, int N1 = FPO_N_SIGMA, int N2 = FPO_N_SH_FOURIER, bool BUF = false, int PARTS = 1,
           int WAVES = cam_waves(MODE)>
-__global__ __launch_bounds__(64 * WAVES, BUF ? 32 / WAVES : 1) void render_cam_kernel(CamLaunch a)
+__global__ __launch_bounds__(64 * WAVES, BUF && PARTS == 1 ? 32 / WAVES : 1) void render_cam_kernel(CamLaunch a)
 {
     static_assert(!BUF || MODE >= 16, "buffer reads serve snapshot records only");
+    static_assert(PARTS == 1 || !SKIP, "the skip modes walk whole rays");
     constexpr int kThreads = 64 * WAVES;
-    constexpr int kTileW = cam_tile_w(WAVES);
-    constexpr int kTileH = cam_tile_h(WAVES);
+    constexpr int kPix = 64 / PARTS;          // pixels of a wave
+    constexpr int kWaveW = wave_tile_w(PARTS);
+    constexpr int kWaveH = wave_tile_h(PARTS);
+    constexpr int kTileW = cam_tile_w(WAVES, PARTS);
+    constexpr int kTileH = cam_tile_h(WAVES, PARTS);
     __shared__ int s_stack[kStackLevels * kThreads];
-    const int lin = xcd_band(blockIdx.x, gridDim.x);
-    if (lin >= a.n_cams * a.cblocks_per_cam) return;
-    const int ci = lin / a.cblocks_per_cam;
-    const int tb = lin - ci * a.cblocks_per_cam;
-    const int bx = tb % a.cbx_per_cam;
-    const int by = tb / a.cbx_per_cam;
+    int bx;
+    const int row = xcd_row(blockIdx.x, a.cbx_per_cam, a.group_rows, bx);
+    const int ci = row / a.crows_per_cam;
+    if (ci >= a.n_cams) return;
+    const int by = row - ci * a.crows_per_cam;
     const int wv = threadIdx.x >> 6;
     const int ln = threadIdx.x & 63;
-    const int px = bx * kTileW + (wv & 1) * 8 + (ln & 7);
-    const int py = by * kTileH + (wv >> 1) * 8 + (ln >> 3);
-    if (px >= a.W || py >= a.H) return;
+    const int part = ln / kPix;               // which part of the chord this lane walks
+    const int lp = ln % kPix;
+    const int px = bx * kTileW + (wv & 1) * kWaveW + lp % kWaveW;
+    const int py = by * kTileH + (wv >> 1) * kWaveH + lp / kWaveW;
+    if (px >= a.W || py >= a.H) return;       // all lanes of a pixel together
 
     const CamDev& cam = a.cam[ci];
     float b[FPO_BASIS_STRIDE];
@@ -235,7 +267,55 @@ __global__ __launch_bounds__(64 * WAVES, BUF ? 32 / WAVES : 1) void render_cam_k
     bool hit;
     if constexpr (SKIP) hit = setup_ray(cam.frame[0], cam.frame[1], cam.frame[2], dx, dy, dz, r);
     else hit = setup_ray_in(a.tree.box_lo, a.tree.box_hi, cam.frame[0], cam.frame[1], cam.frame[2], dx, dy, dz, r);
-    if (hit) {
+    if constexpr (PARTS > 1) {
+        NoStop ns;
+        const float t0 = r.t_len * ((float)part * (1.0f / PARTS));
+        const float t1 = part == PARTS - 1 ? __builtin_inff() : r.t_len * ((float)(part + 1) * (1.0f / PARTS));
+        if (hit) sh9(r.d[0], r.d[1], r.d[2], sh.Y);
+        float Tin = 1.0f;                     // transmittance in front of this part
+        float Tout = 1.0f;                    // and behind it
+        bool alive = true;
+        // pass 0: every part from transmittance 1; pass 1: the part in which the ray stops
+        bool go = hit;
+        for (int pass = 0; pass < 2; ++pass) {
+            if (go) walk<(MODE >= 16), kThreads, true>(a.tree, r, s_stack + threadIdx.x, sh, t1, ns, t0);
+            if (pass == 1) break;
+#pragma unroll
+            for (int q = 0; q < PARTS - 1; ++q) {
+                const float Tq = __shfl(sh.Tr, q * kPix + lp, 64);
+                if (q < part) Tin *= Tq;
+            }
+            alive = !(Tin < a.stop_T);
+            Tout = Tin * sh.Tr;
+            go = hit && alive && part > 0 && Tout < a.stop_T;
+            if (go) {
+                sh.Tr = Tin;
+                sh.C[0] = sh.C[1] = sh.C[2] = 0.0f;
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) sh.C[c] *= Tin;
+            }
+            if (!__any(go)) break;
+        }
+        if (go) Tout = sh.Tr;
+        float C[3] = {0.0f, 0.0f, 0.0f}, Tr = 1.0f;
+#pragma unroll
+        for (int q = 0; q < PARTS; ++q) {
+            const int src = q * kPix + lp;
+            const int on = __shfl((int)alive, src, 64);
+            const float Tq = __shfl(Tout, src, 64);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float Cq = __shfl(sh.C[c], src, 64);
+                C[c] = on ? C[c] + Cq : C[c];
+            }
+            Tr = on ? Tq : Tr;
+        }
+        if (part != 0) return;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) sh.C[c] = C[c];
+        sh.Tr = Tr;
+    } else if (hit) {
         sh9(r.d[0], r.d[1], r.d[2], sh.Y);
         if constexpr (!SKIP) {
             walk<(MODE >= 16), kThreads>(a.tree, r, s_stack + threadIdx.x, sh);
@@ -452,9 +532,34 @@ static int mode_of(const fpo_tree_view* t, const fpo_render_opts* o)
 
 using namespace fpo;
 
-template <int MODE, bool BUF = false>
-static void launch_cam(const dev::CamLaunch& a, int grid, int skip, hipStream_t s)
+// Lanes per ray of a camera launch over `pixels` pixels.  Parts shorten the
+// longest rays, which a launch that does not fill the machine waits for, but
+// cost work (a part's lanes idle where their stretch is empty, and parts behind
+// the ray's end are dropped); the longer the rays, in lattice cells, the later
+// the work wins.  Measured at depths 7 (60 k leaves) / 9 (2 M leaves), one part
+// against the chosen number, in us: F32 snapshot 200x200 117 / 627 -> 42 / 110
+// (16 parts), 400x400 106 / 572 -> 69 (8) / 143 (16), 640x640 107 / 532 -> 109 /
+// 255 (8), 1920x1080 123 / 555 -> 241 / 495 (8), two of them 183 / 692 -> 485 /
+// 973 (8); F32 coefficients 400x400 187 / 973 -> 136 / 433 (16), 640x640 214 /
+// 1077 -> 307 / 708 (16); BF16 coefficients 400x400 167 / 827 -> 174 / 413 (16),
+// 640x640 184 / 885 -> 399 / 872 (16).  The limits double per level between.
+static int ray_parts(int mode, int max_depth, int64_t pixels)
 {
+    if (mode >= 16) return pixels <= (512ll << max_depth) ? 16 : pixels <= (4096ll << max_depth) ? 8 : 1;
+    return pixels <= ((mode == FPO_F32 ? 1536ll : 1024ll) << max_depth) ? 16 : 1;
+}
+
+template <int MODE, bool BUF = false>
+static void launch_cam(const dev::CamLaunch& a, int grid, int skip, int parts, hipStream_t s)
+{
+    switch (parts) {              // 1 with a skip mode
+#define FPO_PARTS(P) case P:                                                                                    \
+        hipLaunchKernelGGL((dev::render_cam_kernel<MODE, false, FPO_N_SIGMA, FPO_N_SH_FOURIER, BUF, P>),         \
+                           dim3(grid), dim3(64 * dev::cam_waves(MODE)), 0, s, a); return
+        FPO_PARTS(8); FPO_PARTS(16);
+#undef FPO_PARTS
+        default: break;
+    }
     if (skip != 0)
         hipLaunchKernelGGL((dev::render_cam_kernel<MODE, true, FPO_N_SIGMA, FPO_N_SH_FOURIER, BUF>), dim3(grid),
                            dim3(64 * dev::cam_waves(MODE)), 0, s, a);
@@ -521,11 +626,12 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
     for (int c = 0; c < 3; ++c) a.bg[c] = opts->bg[c];
     a.stop_T = opts->stop_T;
     const int mode = mode_of(tree, opts);
+    const int parts = variant || skip ? 1 : ray_parts(mode, tree->max_depth, (int64_t)std::min(n_cams, per_launch) * W * H);
     {
         const int waves = variant ? dev::cam_waves(tree->dtype) : dev::cam_waves(mode);
-        const int tw = dev::cam_tile_w(waves), th = dev::cam_tile_h(waves);
+        const int tw = dev::cam_tile_w(waves, parts), th = dev::cam_tile_h(waves, parts);
         a.cbx_per_cam = (W + tw - 1) / tw;
-        a.cblocks_per_cam = a.cbx_per_cam * ((H + th - 1) / th);
+        a.crows_per_cam = (H + th - 1) / th;
     }
     const size_t snap_rec = opts->snapshot_dtype == FPO_F32 ? 128 : 64;   // bytes per leaf record
     // snapshot records within 4 GiB per camera are read with 32-bit offsets
@@ -540,16 +646,28 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
             camera_frame(cam, a.cam[i].frame);
             basis_row(cam.time, (double)tree->layout.period, tree->layout.n_sigma, a.cam[i].basis);
             a.cam[i].snap = opts->snapshot
-                ? static_cast<const char*>(opts->snapshot) + (size_t)(c0 + i) * (size_t)opts->snapshot_cam_stride * snap_rec
+                ? static_cast<const char*>(opts->snapshot) +
+                      (size_t)(c0 + i) * (size_t)opts->snapshot_cam_stride * snap_rec
                 : nullptr;
         }
         a.rgb = rgb_out + (int64_t)c0 * W * H * 3;
         a.Tout = T_out ? T_out + (int64_t)c0 * W * H : nullptr;
         const int64_t total = (int64_t)nc * a.blocks_per_cam;
-        const int64_t ctotal = (int64_t)nc * a.cblocks_per_cam;
+        const int64_t crows = (int64_t)nc * a.crows_per_cam;
+        // Groups of tile rows per XCD.  With a multiple of 8 cameras each XCD
+        // takes whole cameras: equal work, and neighbouring rays share one L2.
+        // Otherwise single rows in turn, which leaves the rows through the
+        // scene's middle to no XCD in particular.  2 M leaves at 1080p: one
+        // camera from Fourier coefficients 2.80 ms in bands of rows and 1.40 ms
+        // in single rows, from a pruned snapshot 0.79 and 0.60 ms, four cameras
+        // 3.88 and 3.50 ms; 16 cameras 12.58 and 12.95 ms.  Groups of two or
+        // more rows were never better than single ones.
+        a.group_rows = nc % 8 == 0 ? (int)((crows + 7) / 8) : 1;
+        const int64_t groups = (crows + a.group_rows - 1) / a.group_rows;
+        const int64_t ctotal = (groups + 7) / 8 * 8 * a.group_rows * a.cbx_per_cam;
         if (ctotal > INT32_MAX - 8) return fail(FPO_E_INVALID, "launch too large");
         const int grid = (int)((total + 7) / 8 * 8);           // skip pre-pass: 16x16 tiles
-        const int cam_grid = (int)((ctotal + 7) / 8 * 8);       // camera kernel tiles
+        const int cam_grid = (int)ctotal;                       // camera kernel tiles
         if (skip != 0) {
             sk.n_cams = nc;
             sk.W = W;
@@ -589,16 +707,16 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
             continue;
         }
         switch (mode) {
-            case FPO_F32: launch_cam<FPO_F32>(a, cam_grid, skip, s); break;
-            case FPO_BF16: launch_cam<FPO_BF16>(a, cam_grid, skip, s); break;
-            case FPO_FP8_E4M3: launch_cam<FPO_FP8_E4M3>(a, cam_grid, skip, s); break;
+            case FPO_F32: launch_cam<FPO_F32>(a, cam_grid, skip, parts, s); break;
+            case FPO_BF16: launch_cam<FPO_BF16>(a, cam_grid, skip, parts, s); break;
+            case FPO_FP8_E4M3: launch_cam<FPO_FP8_E4M3>(a, cam_grid, skip, parts, s); break;
             case dev::kSnapF32:
-                if (snap_buf) launch_cam<dev::kSnapF32, true>(a, cam_grid, skip, s);
-                else launch_cam<dev::kSnapF32>(a, cam_grid, skip, s);
+                if (snap_buf) launch_cam<dev::kSnapF32, true>(a, cam_grid, skip, parts, s);
+                else launch_cam<dev::kSnapF32>(a, cam_grid, skip, parts, s);
                 break;
             case dev::kSnapBF16:
-                if (snap_buf) launch_cam<dev::kSnapBF16, true>(a, cam_grid, skip, s);
-                else launch_cam<dev::kSnapBF16>(a, cam_grid, skip, s);
+                if (snap_buf) launch_cam<dev::kSnapBF16, true>(a, cam_grid, skip, parts, s);
+                else launch_cam<dev::kSnapBF16>(a, cam_grid, skip, parts, s);
                 break;
             default: return fail(FPO_E_INVALID, "unknown render mode");
         }
