@@ -275,6 +275,27 @@ fpo_status fpo_pack_coeffs(const float* src, const int64_t* perm, int64_t n_leav
 fpo_status fpo_render(const fpo_tree_view* tree, const fpo_camera* cams, int32_t n_cams,
                       const fpo_render_opts* opts, float* rgb_out, float* T_out, void* stream);
 
+/* fpo_render without snapshot or skip flags, by decoding first (Sec. 4.1: the
+ * IDFT at time t turns the FPO into a PlenOctree): every leaf is evaluated at
+ * the cameras' distinct times (fpo_bake_times, F32 records, up to 16 times per
+ * pass) into `workspace`, and the views are rendered from those.  The same
+ * images up to FP32 rounding; faster where the views are large against the
+ * tree.
+ *   workspace  device, 128-byte aligned: 2048 bytes, then 128 n_leaves bytes
+ *              for each time of a pass.  More distinct times than fit are
+ *              taken in several passes.  Written by the call's device work;
+ *              calls in flight at once need one each.
+ * FPO_E_UNSUPPORTED for snapshots, skip flags and layouts other than (31, 5).
+ *
+ * fpo_render_decode_bytes: the workspace (at most 4 GiB) with which
+ * fpo_render_decoded is expected to be faster than fpo_render for these
+ * arguments, or 0 where it is not, or not supported.  No device work. */
+int64_t fpo_render_decode_bytes(const fpo_tree_view* tree, const fpo_camera* cams, int32_t n_cams,
+                                const fpo_render_opts* opts);
+fpo_status fpo_render_decoded(const fpo_tree_view* tree, const fpo_camera* cams, int32_t n_cams,
+                              const fpo_render_opts* opts, float* rgb_out, float* T_out, void* workspace,
+                              int64_t workspace_bytes, void* stream);
+
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): fpo_render with
  * the skip modes' scratch taken from a static device array of

@@ -95,6 +95,8 @@ _SIGS = {
     "fpo_pack_coeffs": [_P, _P, _I64, _I64, ctypes.POINTER(Layout), _P, _P],
     "fpo_render": [ctypes.POINTER(TreeView), ctypes.POINTER(CameraC), _I32,
                    ctypes.POINTER(RenderOpts), _P, _P, _P],
+    "fpo_render_decoded": [ctypes.POINTER(TreeView), ctypes.POINTER(CameraC), _I32,
+                           ctypes.POINTER(RenderOpts), _P, _P, _P, _I64, _P],
     "fpo_render_noalloc": [ctypes.POINTER(TreeView), ctypes.POINTER(CameraC), _I32,
                            ctypes.POINTER(RenderOpts), _P, _P, _P],
     "fpo_camera_rays": [_P, _I32, _P, _P, _P, _I64, _P, _P, _P],
@@ -132,7 +134,9 @@ _SIGS = {
     "fpo_coarse_occupancy_at": [_P, _I64, _I32, _P, ctypes.c_int, ctypes.c_float, _P, _P],
 }
 # functions with another return type
-_OTHER = {"fpo_mlp_workspace_floats": ([_I64], ctypes.c_int64)}
+_OTHER = {"fpo_mlp_workspace_floats": ([_I64], ctypes.c_int64),
+          "fpo_render_decode_bytes": ([ctypes.POINTER(TreeView), ctypes.POINTER(CameraC), _I32,
+                                       ctypes.POINTER(RenderOpts)], ctypes.c_int64)}
 
 
 def lib():
@@ -405,7 +409,11 @@ def pack_coeffs(src, perm, n_leaves: int, leaf_stride: int, dst, layout: Optiona
 
 
 def render(tree: DeviceTree, cams, opts: Optional[RenderOpts] = None, rgb=None, T=None, want_T: bool = False):
-    """fpo_render -> (rgb [n][H][W][3], T [n][H][W] or None)."""
+    """fpo_render -> (rgb [n][H][W][3], T [n][H][W] or None).  Views of
+    coefficients that are large against the tree go through fpo_render_decoded
+    with a workspace for the call (at most 4 GiB, from torch's allocator), but
+    not while a HIP graph is captured (it would keep the workspace) and not if
+    the workspace cannot be had."""
     import torch
     opts = opts or make_opts()
     n, H, W = len(cams), int(cams[0].height), int(cams[0].width)
@@ -416,6 +424,16 @@ def render(tree: DeviceTree, cams, opts: Optional[RenderOpts] = None, rgb=None, 
         T = torch.empty((n, H, W), dtype=torch.float32, device=dev)
     tv = tree.view()
     arr = camera_struct(cams)
+    nbytes = lib().fpo_render_decode_bytes(ctypes.byref(tv), arr, n, ctypes.byref(opts))
+    if nbytes > 0 and not torch.cuda.is_current_stream_capturing():
+        try:
+            ws = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:
+            ws = None
+        if ws is not None:
+            _check(lib().fpo_render_decoded(ctypes.byref(tv), arr, n, ctypes.byref(opts), _t_ptr(rgb), _t_ptr(T),
+                                            _t_ptr(ws), nbytes, _stream()))
+            return rgb, T
     _check(lib().fpo_render(ctypes.byref(tv), arr, n, ctypes.byref(opts), _t_ptr(rgb), _t_ptr(T), _stream()))
     return rgb, T
 

@@ -259,8 +259,11 @@ __global__ __launch_bounds__(kBlock, (DT != FPO_F32 && OUT_BF16) ? 3 : 2) void b
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
                 const int k = 4 * kk + kq;
-                const float av = (ta_ok && k < FPO_N_SIGMA) ? brow[k] : 0.0f;
-                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, coef_at(cf, k), acc[0], 0, 0, 0);
+                // the padding takes neither a basis value nor the SH coefficient
+                // stored there (an infinite one would make the density NaN)
+                const bool in = k < FPO_N_SIGMA;
+                const float av = (ta_ok && in) ? brow[k] : 0.0f;
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, in ? coef_at(cf, k) : 0.0f, acc[0], 0, 0, 0);
             }
             // SH rows: K = 5 (padded to 8)
             const float a0 = ta_ok ? brow[kq] : 0.0f;

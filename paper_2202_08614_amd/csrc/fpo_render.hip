@@ -335,6 +335,17 @@ __global__ __launch_bounds__(64 * WAVES, BUF && PARTS == 1 ? 32 / WAVES : 1) voi
     if (a.Tout) a.Tout[pix] = sh.Tr;
 }
 
+// Basis rows of a decode (fpo_render_decoded) from the kernel arguments into
+// its workspace: no copy from host memory is enqueued.
+constexpr int kDecodeTimes = 16;
+struct BasisRows {
+    float row[kDecodeTimes * FPO_BASIS_STRIDE];
+};
+__global__ __launch_bounds__(kBlock) void basis_rows_kernel(BasisRows b, float* out)
+{
+    for (int i = threadIdx.x; i < kDecodeTimes * FPO_BASIS_STRIDE; i += kBlock) out[i] = b.row[i];
+}
+
 struct RaysLaunch {
     TreeDev tree;
     const float* o;
@@ -584,10 +595,11 @@ static bool launch_layout(const dev::CamLaunch& a, int key, int grid, hipStream_
 
 // The body of fpo_render: cameras go out in launches of at most
 // cams_per_launch (<= 16); the skip modes' scratch (opts->workspace) holds
-// one launch's pixels and is reused by every launch of the call.
+// one launch's pixels and is reused by every launch of the call.  snap_index:
+// which of the snapshots each camera reads (null: its own).
 static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams, int32_t n_cams,
                               const fpo_render_opts* opts, float* rgb_out, float* T_out, void* stream,
-                              int cams_per_launch)
+                              int cams_per_launch, const int32_t* snap_index = nullptr)
 {
     fpo_status st = check_tree(tree, opts == nullptr || opts->snapshot == nullptr, true);
     if (st != FPO_OK) return st;
@@ -647,7 +659,7 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
             basis_row(cam.time, (double)tree->layout.period, tree->layout.n_sigma, a.cam[i].basis);
             a.cam[i].snap = opts->snapshot
                 ? static_cast<const char*>(opts->snapshot) +
-                      (size_t)(c0 + i) * (size_t)opts->snapshot_cam_stride * snap_rec
+                      (size_t)(snap_index ? snap_index[c0 + i] : c0 + i) * (size_t)opts->snapshot_cam_stride * snap_rec
                 : nullptr;
         }
         a.rgb = rgb_out + (int64_t)c0 * W * H * 3;
@@ -730,6 +742,137 @@ extern "C" fpo_status fpo_render(const fpo_tree_view* tree, const fpo_camera* ca
 {
     ApiRange api_range_("fpo_render");
     return render_impl(tree, cams, n_cams, opts, rgb_out, T_out, stream, dev::kCamsPerLaunch);
+}
+
+// ---------------------------------------------------------------------------
+// fpo_render_decoded: evaluate every leaf at the cameras' times first
+// (fpo_bake_times into F32 records), then render those.
+//
+// A Fourier-mode ray reads 128 (transparent) to 672 bytes of coefficients and
+// spends 64 to 409 flop per segment; the decoded record is one 128-byte line
+// and 2 to 77 flop, and costs one pass over the store.
+// ---------------------------------------------------------------------------
+namespace fpo {
+constexpr int64_t kDecodeHead = (int64_t)dev::kDecodeTimes * FPO_BASIS_STRIDE * sizeof(float);
+constexpr int64_t kDecodeMaxBytes = 4ll << 30;
+
+// The cameras from c0 on whose distinct times (in times[], at most max_t) fit
+// one decode; returns the camera after them.
+static int decode_group(const fpo_camera* cams, int c0, int n_cams, int max_t, double* times, int& n_t)
+{
+    n_t = 0;
+    int c = c0;
+    for (; c < n_cams; ++c) {
+        int j = 0;
+        while (j < n_t && times[j] != cams[c].time) ++j;
+        if (j == n_t) {
+            if (n_t == max_t) break;
+            times[n_t++] = cams[c].time;
+        }
+    }
+    return c;
+}
+}  // namespace fpo
+
+extern "C" int64_t fpo_render_decode_bytes(const fpo_tree_view* tree, const fpo_camera* cams, int32_t n_cams,
+                                           const fpo_render_opts* opts)
+{
+    if (check_tree(tree, true) != FPO_OK || check_opts(opts, tree, true) != FPO_OK) return 0;
+    if (opts->snapshot || opts->flags != 0 || !cams || n_cams < 1) return 0;
+    for (int i = 0; i < n_cams; ++i)
+        if (!std::isfinite(cams[i].time) || cams[i].width != cams[0].width || cams[i].height != cams[0].height ||
+            cams[i].width < 1 || cams[i].height < 1)
+            return 0;
+    const int64_t rec = tree->n_leaves * 128;
+    if ((kDecodeMaxBytes - kDecodeHead) / rec < 1) return 0;
+    const int cap = (int)std::min<int64_t>((kDecodeMaxBytes - kDecodeHead) / rec, dev::kDecodeTimes);
+    int groups = 0, most = 0;
+    int64_t decoded = 0;
+    for (int c0 = 0; c0 < n_cams; ++groups) {
+        double times[dev::kDecodeTimes];
+        int n_t;
+        c0 = decode_group(cams, c0, n_cams, cap, times, n_t);
+        decoded += n_t;
+        most = std::max(most, n_t);
+    }
+    // Where decoding pays, in us.  A decode streams the store and its records
+    // at 5 TB/s, plus two launches.  What it saves at 2 M leaves of depth 9:
+    // 9.4 ms for 16 views of 1920x1080 (33 Mpixel; 12.6 ms from F32
+    // coefficients, 3.2 ms from decoded records), 930 us for one, 640 us at
+    // 800x800, 290 us at 400x400; at depth 8 (300 k leaves) 240 us at 800x800,
+    // at depth 7 (60 k leaves) 130 us at 800x800 and 67 us at 400x400.
+    const double px = (double)n_cams * cams[0].width * cams[0].height;
+    const double saved = std::ldexp(2.85e-4 * px + 4e-4 * std::min(px, 1048576.0), tree->max_depth - 9);
+    const double bytes = (double)tree->n_leaves * 16 * record_words(tree->dtype, FPO_N_SIGMA, FPO_N_SH_FOURIER) * groups +
+                         (double)rec * decoded;
+    if (saved <= bytes / 5e6 + 12.0 * groups) return 0;
+    return kDecodeHead + most * rec;
+}
+
+extern "C" fpo_status fpo_render_decoded(const fpo_tree_view* tree, const fpo_camera* cams, int32_t n_cams,
+                                         const fpo_render_opts* opts, float* rgb_out, float* T_out, void* workspace,
+                                         int64_t workspace_bytes, void* stream)
+{
+    ApiRange api_range_("fpo_render_decoded");
+    fpo_status st = check_tree(tree, true);
+    if (st != FPO_OK) return st;
+    if ((st = check_opts(opts, tree, true)) != FPO_OK) return st;
+    if (opts->snapshot || opts->flags != 0)
+        return fail(FPO_E_UNSUPPORTED, "fpo_render_decoded renders coefficients without skipping");
+    if (!cams || n_cams < 1) return fail(FPO_E_INVALID, "cams is NULL or n_cams < 1");
+    if (!rgb_out) return fail(FPO_E_INVALID, "rgb_out is NULL");
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 127) != 0)
+        return fail(FPO_E_INVALID, "fpo_render_decoded needs a 128-byte aligned workspace");
+    const int64_t rec = tree->n_leaves * 128;
+    const int cap = (int)std::min<int64_t>((workspace_bytes - kDecodeHead) / rec, dev::kDecodeTimes);
+    if (workspace_bytes < kDecodeHead || cap < 1)
+        return fail(FPO_E_INVALID, "workspace_bytes below the basis rows and one time's records");
+    const int W = cams[0].width, H = cams[0].height;
+    if ((int64_t)W * H > (1ll << 30)) return fail(FPO_E_INVALID, "image too large");
+    for (int i = 0; i < n_cams; ++i) {
+        float fr[12];
+        if (cams[i].width != W || cams[i].height != H)
+            return fail(FPO_E_INVALID, "all cameras of one call must share width and height");
+        if ((st = camera_frame(cams[i], fr)) != FPO_OK) return st;
+    }
+    float* basis = static_cast<float*>(workspace);
+    char* recs = static_cast<char*>(workspace) + kDecodeHead;
+    fpo_tree_view view = *tree;
+    view.leaf_stride = tree->n_leaves;
+    fpo_render_opts o = *opts;
+    o.snapshot = recs;
+    o.snapshot_dtype = FPO_F32;
+    o.snapshot_cam_stride = tree->n_leaves;
+    o.workspace = nullptr;
+    o.workspace_bytes = 0;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    for (int c0 = 0; c0 < n_cams;) {
+        double times[dev::kDecodeTimes];
+        int n_t;
+        const int end = decode_group(cams, c0, n_cams, cap, times, n_t);
+        dev::BasisRows rows;
+        std::memset(&rows, 0, sizeof(rows));
+        for (int j = 0; j < n_t; ++j)
+            basis_row(times[j], (double)tree->layout.period, tree->layout.n_sigma, rows.row + j * FPO_BASIS_STRIDE);
+        hipLaunchKernelGGL(dev::basis_rows_kernel, dim3(1), dim3(dev::kBlock), 0, s, rows, basis);
+        if ((st = launch_status("fpo_render_decoded")) != FPO_OK) return st;
+        if ((st = fpo_bake_times(&view, basis, n_t, FPO_F32, recs, nullptr, stream)) != FPO_OK) return st;
+        // 16 cameras of the group at a time, each with its time's records
+        for (int a = c0; a < end; a += dev::kCamsPerLaunch) {
+            const int n = std::min(end - a, dev::kCamsPerLaunch);
+            int32_t index[dev::kCamsPerLaunch];
+            for (int i = 0; i < n; ++i) {
+                int j = 0;
+                while (times[j] != cams[a + i].time) ++j;
+                index[i] = j;
+            }
+            st = render_impl(&view, cams + a, n, &o, rgb_out + (int64_t)a * W * H * 3,
+                             T_out ? T_out + (int64_t)a * W * H : nullptr, stream, dev::kCamsPerLaunch, index);
+            if (st != FPO_OK) return st;
+        }
+        c0 = end;
+    }
+    return FPO_OK;
 }
 
 // ---------------------------------------------------------------------------
