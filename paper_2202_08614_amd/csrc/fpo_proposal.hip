@@ -3,17 +3,14 @@
 // matrix-core inference the render's skip pre-pass uses.
 //
 // Training step for a batch of n rays (fpo_mlp_loss_grad):
-//   1. mlp_grad_rays_kernel, one thread per ray: encoding, forward pass,
-//      loss, dL/d(outputs) and the back-propagated hidden-layer deltas; the
-//      per-ray vectors every weight gradient needs go to a feature-major
-//      workspace (row f, column ray).
-//   2. mlp_wgrad_kernel: dW = sum over rays of input (x) delta, one thread per
-//      weight, tiles of 16 x 16 weights x 1024 rays staged through LDS; one
-//      partial sum per ray split.
-//   3. mlp_reduce_kernel: the splits summed in a fixed order (deterministic)
-//      into the gradient, and the per-ray losses into the batch loss.
+//   1. mlp_grad_kernel, 64 rays a block at a time: encoding, forward pass, loss,
+//      dL/d(outputs), hidden-layer deltas and the weight gradient on FP32 matrix
+//      cores, activations and deltas in LDS; one partial gradient per block.
+//   2. mlp_reduce_kernel: the partials summed in a fixed order (deterministic)
+//      into the gradient and the batch loss.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <string>
 
@@ -123,16 +120,10 @@ __global__ __launch_bounds__(kBlock) void labels_kernel(LabelLaunch a)
 // ---------------------------------------------------------------------------
 // FP32 training kernels
 // ---------------------------------------------------------------------------
-constexpr int kRowG = 0;                 // encoded inputs, 84 rows
-constexpr int kRowA1 = kRowG + kMlpPE;   // hidden activations of layer 1
-constexpr int kRowA2 = kRowA1 + kMlpH;   // of layer 2
-constexpr int kRowD1 = kRowA2 + kMlpH;   // deltas of layer 1 pre-activations
-constexpr int kRowD2 = kRowD1 + kMlpH;   // of layer 2
-constexpr int kRowGO = kRowD2 + kMlpH;   // dL/d(outputs), 3 rows
-constexpr int kRowLoss = kRowGO + 3;     // per-ray loss
-constexpr int kRows = kRowLoss + 1;
-constexpr int kChunk = 64;               // rays per LDS stage of the weight gradient
-constexpr int kSplit = 1024;             // rays per partial sum
+constexpr int kRows = 344;               // workspace floats per ray (fpo_mlp_workspace_floats)
+constexpr int kChunk = 64;               // rays a block takes at a time
+constexpr int kSplit = 1024;             // workspace: rays per further FPO_MLP_N_PARAMS_PADDED floats
+constexpr int kGradBlocks = 256;         // one block (136 KB of LDS) per CU
 constexpr int kParamsPad = FPO_MLP_N_PARAMS_PADDED;
 constexpr float kQIn = 0.1f;
 constexpr float kQOut = 0.9f;
@@ -224,143 +215,286 @@ __device__ inline float log1p_unit(float u)
     return w == 1.0f ? u : logf(w) * (u / (w - 1.0f));
 }
 
-__global__ __launch_bounds__(kBlock) void mlp_grad_rays_kernel(const float* __restrict__ P, const float* __restrict__ X,
-                                                               const float* __restrict__ Y, const int32_t* __restrict__ idx,
-                                                               int64_t n, int64_t ld, float inv_n, float* __restrict__ ws)
-{
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r >= ld) return;
-    const bool live = r < n;
-    if (!live) {
-        // padding columns: zero, so that the weight gradient may sum whole chunks
-        for (int f = 0; f < kRows; ++f) ws[f * ld + r] = 0.0f;
-        return;
-    }
-    const int64_t row = idx ? (int64_t)idx[r] : r;
-    float x[kMlpIn], g[kMlpPE];
-#pragma unroll
-    for (int c = 0; c < kMlpIn; ++c) x[c] = X[row * kMlpIn + c];
-    const float y0 = Y[row * 3], y1 = Y[row * 3 + 1], y2 = Y[row * 3 + 2];
-    encode_f32(x, g);
-#pragma unroll
-    for (int k = 0; k < kMlpPE; ++k) ws[(kRowG + k) * ld + r] = g[k];
-    Fwd F;
-    forward_f32(P, g, F);
-#pragma unroll
-    for (int k = 0; k < kMlpH; ++k) {
-        ws[(kRowA1 + k) * ld + r] = F.a1[k];
-        ws[(kRowA2 + k) * ld + r] = F.a2[k];
-    }
-    // loss and dL/do: logistic loss on the hit logit, pinball on the sigmoid
-    // of the interval outputs for rays that hit
-    const float o0 = F.o[0];
-    float loss = fmaxf(o0, 0.0f) - y0 * o0 + log1p_unit(expf(-fabsf(o0)));
-    float go[3];
-    go[0] = sigmoid_exact(o0) - y0;
-    const bool hit = y0 > 0.5f;
-    const float yy[2] = {y1, y2};
-    const float qq[2] = {kQIn, kQOut};
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const float s = sigmoid_exact(F.o[1 + e]);
-        const float u = yy[e] - s;
-        const float w = qq[e] - (u < 0.0f ? 1.0f : 0.0f);
-        loss += hit ? u * w : 0.0f;
-        go[1 + e] = hit ? -w * s * (1.0f - s) : 0.0f;
-    }
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-        go[e] *= inv_n;
-        ws[(kRowGO + e) * ld + r] = go[e];
-    }
-    ws[kRowLoss * ld + r] = loss * inv_n;
-    // deltas: d2 = (W3 go) . [z2 > 0]; d1 = (W2 d2) . [z1 > 0]
-    float d2[kMlpH];
-#pragma unroll
-    for (int j = 0; j < kMlpH; ++j) {
-        float v = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 3; ++e) v = fmaf(go[e], P[kP3 + j * 3 + e], v);
-        d2[j] = ((F.m2 >> j) & 1) ? v : 0.0f;
-        ws[(kRowD2 + j) * ld + r] = d2[j];
-    }
-    for (int k = 0; k < kMlpH; ++k) {
-        float v = 0.0f;
-#pragma unroll
-        for (int j = 0; j < kMlpH; ++j) v = fmaf(d2[j], P[kP2 + k * kMlpH + j], v);
-        ws[(kRowD1 + k) * ld + r] = ((F.m1 >> k) & 1) ? v : 0.0f;
-    }
-}
-
-// Tile table of the weight gradient: (layer, k-tile, j-tile).  Layer L's
-// matrix has K_in + 1 rows (the last is the bias, input 1) and J columns.
-struct WTile {
-    int base, J, K1, xrow, drow, kt, jt;
+// LDS of mlp_grad_kernel.  Rows of 68 floats (4 mod 64 banks): 16 lanes along a
+// row times 4 rows one apart, and float4 reads of 16 rows, both spread over all
+// banks.
+constexpr int kLd = 68;
+constexpr int kEncRows = 88;             // 42 arguments padded to 44, sine and cosine
+struct GradLds {
+    float w1[kEncRows][kLd];             // layer 1, rows in encoding order (enc_row)
+    float w2[kMlpH][kLd];
+    float w3[kMlpH * 3];
+    float b1[kMlpH], b2[kMlpH], b3[4];
+    float g[kEncRows][kLd];              // encoded inputs of the block's 64 rays
+    float a1[kMlpH][kLd], a2[kMlpH][kLd];
+    float d1[kMlpH][kLd], d2[kMlpH][kLd];
+    float go[3][kLd];
+    float loss[kBlock / kWave];
 };
+static_assert(sizeof(GradLds) <= 160 * 1024, "LDS of a CU");
 
-__device__ inline WTile wtile(int t)
-{
-    // layer 1: 6 x 4 tiles, layer 2: 5 x 4, layer 3: 5 x 1
-    if (t < 24) return {kP1, kMlpH, kMlpPE + 1, kRowG, kRowD1, t / 4, t % 4};
-    if (t < 44) return {kP2, kMlpH, kMlpH + 1, kRowA1, kRowD2, (t - 24) / 4, (t - 24) % 4};
-    return {kP3, 3, kMlpH + 1, kRowA2, kRowGO, t - 44, 0};
-}
-constexpr int kWTiles = 49;
+// Encoding order: row 8 t + 4 q + kq holds argument 4 t + kq (input
+// (4 t + kq) / 6 times 2^((4 t + kq) % 6)), its sine (q = 0) or cosine (q = 1),
+// so that lane group kq of a wave computes both and feeds one MFMA step with
+// each.  Feature of a row (84 and up: padding, arguments 42 and 43).
+__device__ inline int enc_feature(int row) { return 8 * (row >> 3) + 2 * (row & 3) + ((row >> 2) & 1); }
 
-__global__ __launch_bounds__(256) void mlp_wgrad_kernel(const float* __restrict__ ws, int64_t ld,
-                                                        float* __restrict__ part)
+// Gradient of the batch loss, 64 rays per block and turn, 16 per wave.  All
+// products run on v_mfma_f32_16x16x4f32 (FP32 operands and sums).  Lane (kq, n)
+// works on ray n of its wave; an accumulator tile holds hidden units 16 m + 4
+// kq + r of that ray, which is the operand layout of the next product when its
+// K steps are taken as {16 m + 4 kq + r : kq}, so the layers chain in
+// registers.  Activations and deltas also go to LDS, [unit][ray]; after a
+// barrier wave w forms columns 16 w .. 16 w + 15 of the weight gradients, its
+// K being the block's 64 rays.  Bound by the matrix cores' 412 steps of 32
+// cycles per wave and turn and by the latency around them (one wave per SIMD):
+// a 16,384-ray batch is one turn of 256 blocks.  Before, one thread per ray
+// (64 blocks) wrote 344 floats a ray, which a second kernel read back to form
+// the weight gradient in 16 x 16 tiles: 118 + 48 us for that batch.
+__global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restrict__ P, const float* __restrict__ X,
+                                                          const float* __restrict__ Y, const int32_t* __restrict__ idx,
+                                                          int64_t n_rays, int64_t n_chunks, float inv_n,
+                                                          float* __restrict__ part)
 {
-    __shared__ float xs[16][kChunk + 1];
-    __shared__ float ds[16][kChunk + 1];
-    const WTile T = wtile(blockIdx.x);
-    const int tk = threadIdx.x >> 4, tj = threadIdx.x & 15;
-    const int k = T.kt * 16 + tk, j = T.jt * 16 + tj;
-    const int64_t r0 = (int64_t)blockIdx.y * kSplit;
-    const int64_t r1 = min(r0 + kSplit, ld);
-    float acc = 0.0f;
-    for (int64_t c0 = r0; c0 < r1; c0 += kChunk) {
-        // stage 16 input rows and 16 delta rows of this chunk
-        for (int e = threadIdx.x; e < 16 * kChunk; e += 256) {
-            const int rr = e / kChunk, cc = e % kChunk;
-            const int kk = T.kt * 16 + rr, jj = T.jt * 16 + rr;
-            float xv = 0.0f, dv = 0.0f;
-            if (kk < T.K1 - 1) xv = ws[(int64_t)(T.xrow + kk) * ld + c0 + cc];
-            else if (kk == T.K1 - 1) xv = 1.0f;
-            if (jj < T.J) dv = ws[(int64_t)(T.drow + jj) * ld + c0 + cc];
-            xs[rr][cc] = xv;
-            ds[rr][cc] = dv;
+    __shared__ __align__(16) GradLds S;
+    const int tid = threadIdx.x;
+    const int wv = tid / kWave;
+    const int ln = tid % kWave;
+    const int n = ln & 15;
+    const int kq = ln >> 4;
+    for (int e = tid; e < kEncRows * kMlpH; e += kBlock) {
+        const int k = enc_feature(e / kMlpH);
+        S.w1[e / kMlpH][e % kMlpH] = k < kMlpPE ? P[kP1 + k * kMlpH + e % kMlpH] : 0.0f;
+    }
+    for (int e = tid; e < kMlpH * kMlpH; e += kBlock) S.w2[e / kMlpH][e % kMlpH] = P[kP2 + e];
+    if (tid < kMlpH * 3) S.w3[tid] = P[kP3 + tid];
+    if (tid < kMlpH) {
+        S.b1[tid] = P[kP1 + kMlpPE * kMlpH + tid];
+        S.b2[tid] = P[kP2 + kMlpH * kMlpH + tid];
+    }
+    if (tid < 3) S.b3[tid] = P[kP3 + kMlpH * 3 + tid];
+    __syncthreads();
+
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 acc1[6], acc2[5], acc3[2];         // this wave's columns of dW1, dW2, dW3
+#pragma unroll
+    for (int t = 0; t < 6; ++t) acc1[t] = zero;
+#pragma unroll
+    for (int t = 0; t < 5; ++t) acc2[t] = zero;
+    acc3[0] = acc3[1] = zero;
+    float loss_sum = 0.0f;
+    const int ray = 16 * wv + n;             // column of the LDS rows
+
+    for (int64_t ch = blockIdx.x; ch < n_chunks; ch += gridDim.x) {
+        const int64_t r = ch * kChunk + ray;
+        const bool live = r < n_rays;
+        const int64_t row = live ? (idx ? (int64_t)idx[r] : r) : 0;
+        float x[kMlpIn], y[3];
+#pragma unroll
+        for (int c = 0; c < kMlpIn; ++c) x[c] = live ? X[row * kMlpIn + c] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) y[e] = live ? Y[row * 3 + e] : 0.0f;
+
+        // layer 1
+        f32x4 z[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) z[m][q] = S.b1[16 * m + 4 * kq + q];
+#pragma unroll
+        for (int t = 0; t < kEncRows / 8; ++t) {
+            float arg = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = 4 * t + q;
+                if (i < 6 * kMlpIn) arg = kq == q ? x[i / 6] * (float)(1 << (i % 6)) : arg;
+            }
+            const bool on = live && 4 * t + kq < 6 * kMlpIn;
+            const float sn = on ? sinpif(arg) : 0.0f;
+            const float cs = on ? cospif(arg) : 0.0f;
+            S.g[8 * t + kq][ray] = sn;
+            S.g[8 * t + 4 + kq][ray] = cs;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w1[8 * t + kq][16 * m + n], sn, z[m], 0, 0, 0);
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w1[8 * t + 4 + kq][16 * m + n], cs, z[m], 0, 0, 0);
+        }
+        uint32_t on1 = 0, on2 = 0;           // z > 0 of this lane's 16 units
+        f32x4 a[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[m][q] = live ? fmaxf(z[m][q], 0.0f) : 0.0f;
+                on1 |= (uint32_t)(z[m][q] > 0.0f) << (4 * m + q);
+                S.a1[16 * m + 4 * kq + q][ray] = a[m][q];
+                z[m][q] = S.b2[16 * m + 4 * kq + q];
+            }
+        // layer 2
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w2[16 * k + 4 * kq + q][16 * m + n], a[k][q], z[m],
+                                                                0, 0, 0);
+        // outputs: each lane's 16 units, then the sum over the ray's 4 lanes
+        float o[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int u = 16 * m + 4 * kq + q;
+                const float v = live ? fmaxf(z[m][q], 0.0f) : 0.0f;
+                on2 |= (uint32_t)(z[m][q] > 0.0f) << (4 * m + q);
+                S.a2[u][ray] = v;
+#pragma unroll
+                for (int e = 0; e < 3; ++e) o[e] = fmaf(v, S.w3[u * 3 + e], o[e]);
+            }
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            o[e] += __shfl_xor(o[e], 16, kWave);
+            o[e] += __shfl_xor(o[e], 32, kWave);
+            o[e] += S.b3[e];
+        }
+        // loss and dL/do: logistic loss on the hit logit, pinball on the sigmoid
+        // of the interval outputs for rays that hit
+        float loss = fmaxf(o[0], 0.0f) - y[0] * o[0] + log1p_unit(expf(-fabsf(o[0])));
+        float go[3];
+        go[0] = sigmoid_exact(o[0]) - y[0];
+        const bool hit = y[0] > 0.5f;
+        const float qq[2] = {kQIn, kQOut};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const float sg = sigmoid_exact(o[1 + e]);
+            const float u = y[1 + e] - sg;
+            const float w = qq[e] - (u < 0.0f ? 1.0f : 0.0f);
+            loss += hit ? u * w : 0.0f;
+            go[1 + e] = hit ? -w * sg * (1.0f - sg) : 0.0f;
+        }
+#pragma unroll
+        for (int e = 0; e < 3; ++e) go[e] = live ? go[e] * inv_n : 0.0f;
+        if (kq == 0) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) S.go[e][ray] = go[e];
+            loss_sum += live ? loss * inv_n : 0.0f;
+        }
+        // deltas: d2 = (W3 go) . [z2 > 0]; d1 = (W2 d2) . [z1 > 0]
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int u = 16 * m + 4 * kq + q;
+                float v = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 3; ++e) v = fmaf(go[e], S.w3[u * 3 + e], v);
+                a[m][q] = ((on2 >> (4 * m + q)) & 1) ? v : 0.0f;
+                S.d2[u][ray] = a[m][q];
+                z[m][q] = 0.0f;
+            }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const f32x4 w = *reinterpret_cast<const f32x4*>(&S.w2[16 * m + n][16 * k + 4 * kq]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q], a[k][q], z[m], 0, 0, 0);
+            }
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                S.d1[16 * m + 4 * kq + q][ray] = ((on1 >> (4 * m + q)) & 1) && live ? z[m][q] : 0.0f;
+        __syncthreads();
+
+        // weight gradients: K step (k, q) takes rays 16 k + 4 kq + q
+        const float one = n == 0 ? 1.0f : 0.0f;          // bias tile: row 0
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int at = 16 * k + 4 * kq;
+            const f32x4 e1 = *reinterpret_cast<const f32x4*>(&S.d1[16 * wv + n][at]);
+            const f32x4 e2 = *reinterpret_cast<const f32x4*>(&S.d2[16 * wv + n][at]);
+            const f32x4 e3 = n < 3 ? *reinterpret_cast<const f32x4*>(&S.go[n][at]) : zero;
+#pragma unroll
+            for (int t = 0; t < 6; ++t) {
+                f32x4 v;
+                if (t < 5) {
+                    v = *reinterpret_cast<const f32x4*>(&S.g[16 * t + n][at]);
+                } else {                                 // rows 80 .. 87, then the bias row
+                    v = n == 8 ? f32x4{1.0f, 1.0f, 1.0f, 1.0f} : zero;
+                    if (n < 8) v = *reinterpret_cast<const f32x4*>(&S.g[80 + n][at]);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[q], e1[q], acc1[t], 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(&S.a1[16 * t + n][at]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[q], e2[q], acc2[t], 0, 0, 0);
+            }
+            const f32x4 v = *reinterpret_cast<const f32x4*>(&S.a2[16 * wv + n][at]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc2[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(one, e2[q], acc2[4], 0, 0, 0);
+                acc3[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[q], e3[q], acc3[0], 0, 0, 0);
+                acc3[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(one, e3[q], acc3[1], 0, 0, 0);
+            }
         }
         __syncthreads();
-#pragma unroll 16
-        for (int cc = 0; cc < kChunk; ++cc) acc = fmaf(xs[tk][cc], ds[tj][cc], acc);
-        __syncthreads();
     }
-    if (k < T.K1 && j < T.J) part[(int64_t)blockIdx.y * kParamsPad + T.base + k * T.J + j] = acc;
+
+    float* out = part + (int64_t)blockIdx.x * kParamsPad;
+    const int j = 16 * wv + n;
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int p = 16 * t + 4 * kq + q;
+            const int k = p < kEncRows ? enc_feature(p) : kMlpPE;
+            if (p <= kEncRows && (p == kEncRows || k < kMlpPE)) out[kP1 + k * kMlpH + j] = acc1[t][q];
+        }
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 16 * t + 4 * kq + q;
+            if (k <= kMlpH) out[kP2 + k * kMlpH + j] = acc2[t][q];
+        }
+    if (n < 3) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[kP3 + (16 * wv + 4 * kq + q) * 3 + n] = acc3[0][q];
+        if (wv == 0 && kq == 0) out[kP3 + kMlpH * 3 + n] = acc3[1][0];
+    }
+    loss_sum = wave_sum(loss_sum);
+    if (ln == 0) S.loss[wv] = loss_sum;
+    __syncthreads();
+    if (tid == 0) out[FPO_MLP_N_PARAMS] = (S.loss[0] + S.loss[1]) + (S.loss[2] + S.loss[3]);
 }
 
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ part, int n_split,
-                                                         const float* __restrict__ loss_row, int64_t ld,
+// grad += the partials' sum, loss += their last float's.  32 parameters a
+// block, 8 threads each over every eighth partial (as many loads in flight),
+// combined in a fixed order.
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ part, int n_part,
                                                          float* __restrict__ grad, float* __restrict__ loss)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (blockIdx.x < gridDim.x - 1) {
-        if (i < FPO_MLP_N_PARAMS) {
-            float s = 0.0f;
-            for (int sp = 0; sp < n_split; ++sp) s += part[(int64_t)sp * kParamsPad + i];
-            grad[i] += s;
-        }
-        return;
-    }
-    __shared__ float red[256];
+    __shared__ float red[8][32];
+    const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
+    const int i = blockIdx.x * 32 + c;
     float s = 0.0f;
-    for (int64_t r = threadIdx.x; r < ld; r += 256) s += loss_row[r];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (i < kParamsPad) {
+#pragma unroll 8
+        for (int b = q; b < n_part; b += 8) s += part[(int64_t)b * kParamsPad + i];
     }
-    if (threadIdx.x == 0) loss[0] += red[0];
+    red[q][c] = s;
+    __syncthreads();
+    if (q != 0 || i >= kParamsPad) return;
+    s = ((red[0][c] + red[1][c]) + (red[2][c] + red[3][c])) + ((red[4][c] + red[5][c]) + (red[6][c] + red[7][c]));
+    if (i < FPO_MLP_N_PARAMS) grad[i] += s;
+    else loss[0] += s;
 }
 
 // ---------------------------------------------------------------------------
@@ -498,21 +632,18 @@ extern "C" fpo_status fpo_mlp_loss_grad(const float* params, const float* inputs
     if (n < 1) return fail(FPO_E_INVALID, "n must be >= 1");
     if (!params || !inputs || !labels || !workspace || !grad || !loss) return fail(FPO_E_INVALID, "NULL device pointer");
     if ((reinterpret_cast<uintptr_t>(workspace) & 15) != 0) return fail(FPO_E_INVALID, "workspace must be 16-byte aligned");
-    const int64_t ld = mlp_ld(n);
-    const int64_t n_split = mlp_splits(n);
-    if (ld > (int64_t)1 << 30) return fail(FPO_E_INVALID, "batch too large");
+    if (mlp_ld(n) > (int64_t)1 << 30) return fail(FPO_E_INVALID, "batch too large");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    float* part = workspace + (int64_t)dev::kRows * ld;
-    const int64_t g1 = (ld + dev::kBlock - 1) / dev::kBlock;
-    hipLaunchKernelGGL(dev::mlp_grad_rays_kernel, dim3((unsigned)g1), dim3(dev::kBlock), 0, s, params, inputs, labels,
-                       idx, n, ld, 1.0f / (float)n, workspace);
-    fpo_status st = launch_status("fpo_mlp_loss_grad (rays)");
+    // a block takes every kGradBlocks-th chunk of 64 rays; the partials (39 KB
+    // per block, at most one block per chunk) fit the workspace's 86 KB a chunk
+    const int64_t chunks = mlp_ld(n) / dev::kChunk;
+    const int blocks = (int)std::min<int64_t>(chunks, dev::kGradBlocks);
+    hipLaunchKernelGGL(dev::mlp_grad_kernel, dim3(blocks), dim3(dev::kBlock), 0, s, params, inputs, labels, idx, n,
+                       chunks, 1.0f / (float)n, workspace);
+    fpo_status st = launch_status("fpo_mlp_loss_grad");
     if (st != FPO_OK) return st;
-    hipLaunchKernelGGL(dev::mlp_wgrad_kernel, dim3(dev::kWTiles, (unsigned)n_split), dim3(256), 0, s, workspace, ld, part);
-    if ((st = launch_status("fpo_mlp_loss_grad (weights)")) != FPO_OK) return st;
-    const int g3 = (FPO_MLP_N_PARAMS + 255) / 256 + 1;
-    hipLaunchKernelGGL(dev::mlp_reduce_kernel, dim3(g3), dim3(256), 0, s, part, (int)n_split,
-                       workspace + (int64_t)dev::kRowLoss * ld, ld, grad, loss);
+    hipLaunchKernelGGL(dev::mlp_reduce_kernel, dim3((dev::kParamsPad + 31) / 32), dim3(256), 0, s, workspace, blocks,
+                       grad, loss);
     return launch_status("fpo_mlp_loss_grad (reduce)");
 }
 
