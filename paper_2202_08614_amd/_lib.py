@@ -706,10 +706,13 @@ def dft_frames(frames, n_leaves: int, literal: bool = False, coeffs=None, sigma_
     """fpo_dft_frames: frames [T][stride][32] -> (F32 records [stride][48][4], sigma_max [stride])."""
     import torch
     T, stride = int(frames.shape[0]), int(frames.shape[1])
+    # the call writes the first n_leaves slots whole; slots past them are zero
     if coeffs is None:
-        coeffs = torch.zeros((stride, record_words(FPO_F32), 4), dtype=torch.float32, device=frames.device)
+        coeffs = torch.empty((stride, record_words(FPO_F32), 4), dtype=torch.float32, device=frames.device)
+        coeffs[int(n_leaves):].zero_()
     if sigma_max is None:
-        sigma_max = torch.zeros((stride,), dtype=torch.float32, device=frames.device)
+        sigma_max = torch.empty((stride,), dtype=torch.float32, device=frames.device)
+        sigma_max[int(n_leaves):].zero_()
     _check(lib().fpo_dft_frames(_t_ptr(frames), T, int(n_leaves), stride, 1 if literal else 0, _t_ptr(coeffs),
                                 _t_ptr(sigma_max), _stream()))
     return coeffs, sigma_max

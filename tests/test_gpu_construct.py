@@ -110,6 +110,31 @@ def test_dft_matches_oracle(dev, T, literal):
     assert np.array_equal(smax.cpu().numpy()[:L], vals[:, :L, 0].max(0))
 
 
+@pytest.mark.parametrize("T,L,pad", [(1, 1, 0), (2, 7, 1), (3, 8, 0), (4, 9, 0), (5, 31, 4), (8, 33, 0), (120, 40, 2),
+                                     (9, 2048 * 32 + 65, 3)])
+def test_dft_edges(dev, T, L, pad):
+    """Frame counts around the frames in flight, leaf counts around a wave's
+    eight and a block's 32, and past one turn of the grid; slots past the last
+    leaf come back zero, the caller's own buffers keep what lies there."""
+    import torch
+    rng = np.random.default_rng(100 * T + L)
+    vals = np.full((T, L + pad, 32), np.nan, np.float32)
+    vals[:, :L] = 0.0
+    vals[:, :L, :28] = rng.standard_normal((T, L, 28)).astype(np.float32)
+    note(f"fpo_dft_frames edges T={T} L={L}")
+    frames = torch.from_numpy(vals).to(dev)
+    coeffs, smax = _lib.dft_frames(frames, L)
+    own = torch.full_like(coeffs, 7.0)
+    _lib.dft_frames(frames, L, coeffs=own)
+    torch.cuda.synchronize()
+    got = coeffs.cpu().numpy().reshape(L + pad, 192)
+    want = dft.dft(vals[:, :L, :28])
+    assert np.all(np.abs(got[:L, :166] - want) <= _dft_bound(vals[:, :L], T) + 1e-30)
+    assert np.all(got[:L, 166:] == 0.0) and np.all(got[L:] == 0.0)
+    assert np.array_equal(smax.cpu().numpy(), np.concatenate([vals[:, :L, 0].max(0), np.zeros(pad, np.float32)]))
+    assert torch.equal(own[:L], coeffs[:L]) and bool((own[L:] == 7.0).all())
+
+
 def test_bake_then_dft_round_trip(dev):
     """Baking a tree at t = 0 .. 59 and taking the DFT returns its coefficients."""
     import torch
