@@ -99,6 +99,7 @@ typedef enum { FPO_F32 = 0, FPO_BF16 = 1, FPO_FP8_E4M3 = 2 } fpo_dtype;
 #define FPO_RENDER_SKIP_PROPOSAL 2
 #define FPO_RAYS_RECORD 4          /* fpo_render_rays / fpo_render_backward: segment records */
 #define FPO_RECORD_BYTES 32        /* one recorded segment in the workspace */
+#define FPO_RECORD_MAX_RAYS 32768  /* rays of a recorded batch */
 
 /* Fourier / SH sizes, period and density scale.  Only (31, 5, 2) is compiled. */
 typedef struct {
@@ -323,10 +324,9 @@ fpo_status fpo_camera_rays(const float* cam_table, int32_t n_cams, const int32_t
 /* Render arbitrary rays (Sec. 4.1: the per-pixel render of fpo_render for
  * rays given directly, each at its own time, as the fine-tuning of Sec. 4.3
  * draws them from the training images); ray r uses basis row t_idx[r] of the
- * Eq. 8 table that fpo_time_basis fills on the host in FP64.  In Fourier mode
- * from an F32 store, batches of at most 32768 rays run one ray per wave (the
- * lanes share each leaf's coefficients), larger ones one ray per lane; the
- * two agree to FP32 rounding.
+ * Eq. 8 table that fpo_time_basis fills on the host in FP64.  Small
+ * batches cut each ray into 16 or 32 parts that are walked side by side and
+ * composed, large ones walk it whole; the two agree to FP32 rounding.
  *   o, d   device [n_rays][3] F32 (d is normalised by the kernel; |d| > 0).
  *   t_idx  device [n_rays] int32 in [0, n_t).
  *   basis  device [n_t][FPO_BASIS_STRIDE] F32 (fpo_time_basis).

@@ -23,26 +23,29 @@ from . import _lib
 
 class FPORender(torch.autograd.Function):
     """rgb = render(coeffs) for given rays; coeffs are the F32 leaf records
-    of `tree` (passed explicitly so that autograd tracks them).  With
-    FPO_RAYS_RECORD in opts the forward's segment records in opts.workspace
-    serve the backward, so the same opts must not be reused for another
-    forward before backward() runs."""
+    of `tree` (passed explicitly so that autograd tracks them).  A forward
+    whose gradient is wanted keeps its segment records for the backward (up to
+    64 MiB, as a saved tensor) where the batch allows it.  With FPO_RAYS_RECORD
+    in opts they go to opts.workspace, and the same opts must not be reused for
+    another forward before backward() runs."""
 
     @staticmethod
     def forward(ctx, coeffs, tree: _lib.DeviceTree, o, d, t_idx, basis, opts: _lib.RenderOpts):
         if coeffs.data_ptr() != tree.coeffs.data_ptr():
             raise ValueError("coeffs must be the tree's coefficient store")
-        rgb, _ = _lib.render_rays(tree, o, d, t_idx, basis, opts)
-        ctx.save_for_backward(o, d, t_idx, basis, rgb)
+        ws = _lib.spare_record_workspace(tree, opts, int(o.shape[0]), o.device) if ctx.needs_input_grad[0] else None
+        rgb, _ = _lib.render_rays(tree, o, d, t_idx, basis, opts if ws is None else _lib.with_records(opts, ws))
+        ctx.save_for_backward(o, d, t_idx, basis, rgb, ws)
         ctx.tree = tree
         ctx.opts = opts
         return rgb
 
     @staticmethod
     def backward(ctx, grad_rgb):
-        o, d, t_idx, basis, rgb = ctx.saved_tensors
+        o, d, t_idx, basis, rgb, ws = ctx.saved_tensors
         grad = torch.zeros_like(ctx.tree.coeffs)
-        _lib.render_backward(ctx.tree, o, d, t_idx, basis, rgb, grad_rgb.contiguous(), grad, ctx.opts)
+        opts = ctx.opts if ws is None else _lib.with_records(ctx.opts, ws)
+        _lib.render_backward(ctx.tree, o, d, t_idx, basis, rgb, grad_rgb.contiguous(), grad, opts)
         return grad, None, None, None, None, None, None
 
 

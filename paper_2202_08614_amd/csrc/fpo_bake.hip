@@ -109,10 +109,7 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const float4* src, int
             if (4 * g + 3 >= kCoeff) w[p].w = 0.0f;
         }
         // maximum over the leaf's 16 lanes (one DPP row)
-        mx = fmaxf(mx, dpp_move<0xb1>(mx));
-        mx = fmaxf(mx, dpp_move<0x4e>(mx));
-        mx = fmaxf(mx, dpp_move<0x141>(mx));
-        mx = fmaxf(mx, dpp_move<0x140>(mx));
+        mx = row_max(mx);
         float s = (DT == FPO_BF16) ? mx : mx / 448.0f;
         if (mx == 0.0f) s = 1.0f;
         if (g0 == 0) scale[l] = s;

@@ -551,6 +551,13 @@ struct Shade {
         }
     }
 
+    // Composite from transmittance Tin and no colour.
+    __device__ inline void restart(float Tin)
+    {
+        Tr = Tin;
+        C[0] = C[1] = C[2] = 0.0f;
+    }
+
     // Front-to-back compositing of a segment of transmittance e and SH sums h;
     // true once the ray's transmittance is below stop_T.
     __device__ inline bool composite(float e, const float* h)
@@ -564,29 +571,212 @@ struct Shade {
 };
 
 // --------------------------------------------------------------------------
-// One ray per wave, for small ray batches and the backward: a fine-tuning
-// batch of a few thousand rays fills only a few dozen wave slots at one ray
-// per lane, and one lane scattering 166 gradients per sample is bound by the
-// number of lines its atomics touch.  All
-// 64 lanes walk the same ray (uniform branches, broadcast child loads).  The
-// 166 F32 coefficients of a leaf are spread over the lanes, lane l holding
-// q = l, l + 64, l + 128, so a record is read (and a gradient record
-// written) with three coalesced accesses, and the dot products of Eq. 7 and
-// Eq. 9 with the SH sums of Eq. 1 become wave sums.
+// PARTS lanes per ray, lane part * (64 / PARTS) + slot of the wave the part-th
+// of ray `slot`: each walks an equal part of its chord from transmittance 1;
+// the parts' colours and transmittances are then composed front to back,
+// C = C_0 + T_0 (C_1 + T_1 (...)).  A launch of few waves lasts as long as its
+// longest rays (each step waits for two or three dependent reads, about 2 us),
+// and this cuts them.  The stop rule stays the walk's: the part in which the
+// ray's transmittance falls below stop_T is walked again from the transmittance
+// it is entered with, the later ones are dropped.
 // --------------------------------------------------------------------------
+struct PartFront {
+    float Tin;       // transmittance in front of the part
+    float Tout;      // and behind it
+    bool alive;      // the ray reaches the part
+    bool redone;     // the part was walked from Tin (its records and sums are the whole ray's)
+};
 
-// fpo_render_rays runs batches of at most this many rays one ray per wave (F32
-// Fourier mode); above it one ray per lane fills the machine and is faster.
-// The backward always runs one ray per wave: its coalesced gradient writes
-// beat one ray per lane at every batch size.
-constexpr int64_t kWaveRayBatch = 32768;
+// Every lane of a ray calls this together.  On return sh.C is the part's
+// contribution to the ray's colour, where alive.
+template <int PARTS, bool TWO, int STRIDE, class Sh>
+__device__ inline PartFront walk_parts(const TreeDev& T, const Ray& r, int* stk, Sh& sh, bool hit, int part, int slot)
+{
+    constexpr int kSlots = 64 / PARTS;
+    NoStop ns;
+    const float t0 = r.t_len * ((float)part * (1.0f / PARTS));
+    const float t1 = part == PARTS - 1 ? __builtin_inff() : r.t_len * ((float)(part + 1) * (1.0f / PARTS));
+    PartFront f{1.0f, 1.0f, true, false};
+    // pass 0: every part from transmittance 1; pass 1: the part in which the ray stops
+    bool go = hit;
+    for (int pass = 0; pass < 2; ++pass) {
+        if (go) walk<TWO, STRIDE, true>(T, r, stk, sh, t1, ns, t0);
+        if (pass == 1) break;
+#pragma unroll
+        for (int q = 0; q < PARTS - 1; ++q) {
+            const float Tq = __shfl(sh.Tr, q * kSlots + slot, 64);
+            if (q < part) f.Tin *= Tq;
+        }
+        f.alive = !(f.Tin < sh.stop_T);
+        f.Tout = f.Tin * sh.Tr;
+        go = hit && f.alive && part > 0 && f.Tout < sh.stop_T;
+        if (go) {
+            sh.restart(f.Tin);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sh.C[c] *= f.Tin;
+        }
+        if (!__any(go)) break;
+    }
+    f.redone = go;
+    if (go) f.Tout = sh.Tr;
+    return f;
+}
 
-// Sum over the wave.  Within each row of 16 lanes, four DPP steps add lane
-// pairs, quads, half rows and rows (every lane adds the same two partial sums,
-// a + b and b + a being equal in IEEE arithmetic, so the row's lanes agree);
-// the four row sums are then read into scalar registers and added in one
-// fixed order.  All lanes hold the same bits, branches on the result stay
-// uniform, and no step goes through LDS.
+// The ray's colour and transmittance, left in sh on all its lanes.
+template <int PARTS, class Sh>
+__device__ inline void compose_parts(const PartFront& f, Sh& sh, int part, int slot)
+{
+    constexpr int kSlots = 64 / PARTS;
+    float C[3] = {0.0f, 0.0f, 0.0f}, Tr = 1.0f;
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) {
+        const int src = q * kSlots + slot;
+        const int on = __shfl((int)f.alive, src, 64);
+        const float Tq = __shfl(f.Tout, src, 64);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float Cq = __shfl(sh.C[c], src, 64);
+            C[c] = on ? C[c] + Cq : C[c];
+        }
+        Tr = on ? Tq : Tr;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sh.C[c] = C[c];
+    sh.Tr = Tr;
+}
+
+// --------------------------------------------------------------------------
+// Segment records of PARTS lanes per ray.  A record is {leaf, delta, T, C[3],
+// 0, 0} of a segment with positive optical depth, T and C the transmittance and
+// colour in front of it (FPO_RAYS_RECORD).  While a part is walked they are the
+// part's own and wait in LDS, kLaneRecs at a time; PartRecords::finish turns
+// them into the ray's.  The forward that writes the records and the backward
+// that walks rays without them both take T and C from here, so the two agree to
+// the last bit however many records a caller keeps.
+// --------------------------------------------------------------------------
+constexpr int kLaneRecs = 8;
+constexpr int kRecStage = kLaneRecs * 2 * kWave;     // float4 of LDS per wave
+
+struct RecShade : Shade<FPO_F32> {
+    float4* stage;       // this lane's LDS slots: record k at stage[128 k], stage[128 k + 64]
+    int n;               // records so far
+    int k0;              // the first one that is kept
+
+    __device__ inline bool segment(int leaf, float t0, float t1)
+    {
+        using E = LeafEval<FPO_F32>;
+        float k[E::kSigmaWords * E::W], h[3], scale;
+        const float delta = t1 - t0;
+        const float sig = T.sigma_scale * fmaxf(E::sigma(T, leaf, b, k, scale), 0.0f);
+        if (!(sig * delta > 0.0f)) return false;   // transparent: contributes nothing
+        const int i = n - k0;
+        if (i >= 0 && i < kLaneRecs) {
+            stage[128 * i] = make_float4(__int_as_float(leaf), delta, Tr, C[0]);
+            stage[128 * i + 64] = make_float4(C[1], C[2], 0.0f, 0.0f);
+        }
+        ++n;
+        E::colour(T, leaf, b, Y, k, scale, h);
+        return composite(__expf(-sig * delta), h);
+    }
+    __device__ inline void restart(float Tin)
+    {
+        Shade<FPO_F32>::restart(Tin);
+        n = 0;
+    }
+};
+
+struct PartRecords {
+    PartFront f;
+    float Cin[3];        // colour in front of the part
+    int mine;            // records of the part, 0 if the ray does not reach it
+    int first;           // records of the ray in front of it
+    int total;           // records of the ray
+
+    __device__ inline void finish(float4& x0, float4& x1) const
+    {
+        const float w = f.redone ? 1.0f : f.Tin;
+        x0.z *= w;
+        x0.w = fmaf(w, x0.w, Cin[0]);
+        x1.x = fmaf(w, x1.x, Cin[1]);
+        x1.y = fmaf(w, x1.y, Cin[2]);
+    }
+};
+
+// Walk a ray's parts; the first kLaneRecs records of each are staged.  sh.C is
+// the part's contribution (compose_parts).
+template <int PARTS>
+__device__ inline PartRecords collect_records(const TreeDev& T, const Ray& r, int* stk, float4* stage, RecShade& sh,
+                                              bool hit, float stop_T, int part, int slot)
+{
+    constexpr int kSlots = kWave / PARTS;
+    sh.stage = stage;
+    sh.k0 = 0;
+    sh.stop_T = stop_T;
+    sh.restart(1.0f);
+    if (hit) sh9(r.d[0], r.d[1], r.d[2], sh.Y);
+    PartRecords p;
+    p.f = walk_parts<PARTS, true, kWave>(T, r, stk, sh, hit, part, slot);
+    p.Cin[0] = p.Cin[1] = p.Cin[2] = 0.0f;
+    p.mine = p.f.alive ? sh.n : 0;
+    p.first = p.total = 0;
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) {
+        const int src = q * kSlots + slot;
+        const int nq = __shfl(p.mine, src, kWave);
+        const bool on = __shfl((int)p.f.alive, src, kWave) && q < part;
+        p.first += q < part ? nq : 0;
+        p.total += nq;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float Cq = __shfl(sh.C[c], src, kWave);
+            p.Cin[c] = on ? p.Cin[c] + Cq : p.Cin[c];
+        }
+    }
+    return p;
+}
+
+// Stage records k0 .. k0 + kLaneRecs - 1 of the part: the same walk again, to
+// the end of what it records (the part may stop before its chord does).
+template <int PARTS>
+__device__ inline void restage(const TreeDev& T, const Ray& r, int* stk, RecShade& sh, const PartRecords& p, int part,
+                               int k0)
+{
+    NoStop ns;
+    const float t0 = r.t_len * ((float)part * (1.0f / PARTS));
+    const float t1 = part == PARTS - 1 ? __builtin_inff() : r.t_len * ((float)(part + 1) * (1.0f / PARTS));
+    sh.k0 = k0;
+    sh.restart(p.f.redone ? p.f.Tin : 1.0f);
+    walk<true, kWave, true>(T, r, stk, sh, t1, ns, t0);
+}
+
+__device__ inline void load_basis(const float* basis, int ti, float* b)
+{
+    const float4* brow = reinterpret_cast<const float4*>(basis + (int64_t)ti * FPO_BASIS_STRIDE);
+#pragma unroll
+    for (int i = 0; i < FPO_BASIS_STRIDE / 4; ++i) {
+        const float4 v = brow[i];
+        b[4 * i] = v.x; b[4 * i + 1] = v.y; b[4 * i + 2] = v.z; b[4 * i + 3] = v.w;
+    }
+}
+
+// --------------------------------------------------------------------------
+// The backward: a row of 16 lanes takes one segment at a time, a wave four.
+// One lane scattering 166 gradients per sample is bound by the number of lines
+// its atomics touch; here the 166 F32 coefficients of a leaf are spread over
+// the lanes, lane l holding q = l, l + 16, ..., l + 160, so a record is read
+// (and a gradient record written) in 64-byte pieces, and the dot products of
+// Eq. 7 and Eq. 9 with the SH sums of Eq. 1 become row sums.  With the whole
+// wave on one segment, 32768 recorded rays took 171 (depth 6) to 155 us (depth
+// 8).
+// --------------------------------------------------------------------------
+constexpr int kRow = 16;                  // lanes per ray
+constexpr int kWaveRays = kWave / kRow;
+
+// Sums and maxima over a row of 16 lanes: four DPP steps combine lane pairs,
+// quads, half rows and rows.  Every lane adds the same two partial sums, a + b
+// and b + a being equal in IEEE arithmetic, so all lanes of the row hold the
+// same bits, branches on the result stay uniform, and no step goes through LDS.
 template <int CTRL>
 __device__ inline float dpp_move(float v)
 {
@@ -597,12 +787,25 @@ __device__ inline float dpp_add(float v)
 {
     return v + dpp_move<CTRL>(v);
 }
-__device__ inline float wave_sum(float v)
+__device__ inline float row_sum(float v)
 {
     v = dpp_add<0xb1>(v);     // quad_perm [1, 0, 3, 2]: pairs
     v = dpp_add<0x4e>(v);     // quad_perm [2, 3, 0, 1]: quads
     v = dpp_add<0x141>(v);    // row_half_mirror: half rows
-    v = dpp_add<0x140>(v);    // row_mirror: rows
+    return dpp_add<0x140>(v); // row_mirror: rows
+}
+__device__ inline float row_max(float v)
+{
+    v = fmaxf(v, dpp_move<0xb1>(v));
+    v = fmaxf(v, dpp_move<0x4e>(v));
+    v = fmaxf(v, dpp_move<0x141>(v));
+    return fmaxf(v, dpp_move<0x140>(v));
+}
+// Over the wave: the four row sums read into scalar registers and added in one
+// fixed order.
+__device__ inline float wave_sum(float v)
+{
+    v = row_sum(v);
     const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 0));
     const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 16));
     const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32));
@@ -610,146 +813,110 @@ __device__ inline float wave_sum(float v)
     return (r0 + r1) + (r2 + r3);
 }
 
-// This lane's coefficient slots for one ray: q = lane + 64 s, s < 3.  A
+// This lane's coefficient slots for one ray: q = lane + 16 s, s < 11.  A
 // density slot (q < 31) weighs b_q; an SH slot q = 31 + (9 c + j) 5 + i
 // weighs Y_j b_i and feeds channel c.
-struct WaveSlots {
-    float w[3];
-    int c[3];        // channel of an SH slot, -1 density, -2 past the 166 coefficients
+constexpr int kRowSlots = (FPO_N_COEFF + kRow - 1) / kRow;
+struct RowSlots {
+    float w[kRowSlots];
     __device__ inline void init(int lane, const float* brow, const float* Y)
     {
 #pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const int q = lane + kWave * s;
+        for (int s = 0; s < kRowSlots; ++s) {
+            const int q = lane + kRow * s;
             if (q >= FPO_N_COEFF) {
                 w[s] = 0.0f;
-                c[s] = -2;
             } else if (q < FPO_N_SIGMA) {
                 w[s] = brow[q];
-                c[s] = -1;
             } else {
-                const int u = q - FPO_N_SIGMA;
-                const int ch = u / (FPO_N_SH * FPO_N_SH_FOURIER);
-                const int rem = u - ch * (FPO_N_SH * FPO_N_SH_FOURIER);
+                const int rem = (q - FPO_N_SIGMA) % (FPO_N_SH * FPO_N_SH_FOURIER);
                 const int j = rem / FPO_N_SH_FOURIER;
                 const int i = rem - j * FPO_N_SH_FOURIER;
                 float yj = Y[0];
 #pragma unroll
                 for (int jj = 1; jj < FPO_N_SH; ++jj) yj = j == jj ? Y[jj] : yj;
                 w[s] = yj * brow[i];
-                c[s] = ch;
             }
         }
     }
+    // What slot s of `lane` feeds: -1 the density, 0 .. 2 a channel, -2 nothing
+    // (a constant for most s once the loops are unrolled).
+    __device__ static inline int feeds(int lane, int s)
+    {
+        const int lo = kRow * s, hi = lo + kRow - 1;   // q of the row's first and last lane
+        const int cut[4] = {FPO_N_SIGMA, FPO_N_SIGMA + 45, FPO_N_SIGMA + 90, FPO_N_COEFF};
+        int f = -2;
+#pragma unroll
+        for (int c = 3; c >= 0; --c) {
+            if (hi < cut[c]) f = c - 1;
+            else if (lo < cut[c]) f = lane < cut[c] - lo ? c - 1 : f;
+        }
+        return f;
+    }
 };
 
-// Fourier-mode F32 shading of one ray by a whole wave.  GRAD = false
-// composites front to back (C, Tr).  GRAD = true recomputes the same walk and
-// scatters dL/dk: with C the colour accumulated so far, Cf the forward
-// pass's final colour and g = dL/dCf,
+// Fourier-mode F32 shading of one segment by a row of lanes, scattering dL/dk:
+// with C the colour accumulated with it, Cf the forward pass's final colour and
+// g = dL/dCf,
 //     dL/dsigma_i = delta_i s sum_c g_c (T_{i+1} col_c - (Cf_c - C_c)),
 //     dL/dh_c     = g_c T_i alpha_i col_c (1 - col_c),
 // then dL/dk = dL/dsigma b_q (density) or dL/dh_c Y_j b_i (SH).
-//
-// Segment records (REC, forward only): every segment with positive optical
-// depth is written as {leaf, delta, T_i, C_i[3]} (C_i the colour accumulated
-// before it), 32 bytes, so that the backward can treat the ray's segments
-// independently of each other.
-template <bool GRAD, bool REC = false>
-struct WaveShade {
-    static_assert(!(GRAD && REC), "segment records are written by the forward");
+struct RowGrad {
     const TreeDev& T;
-    WaveSlots sl;
-    int lane;
-    float Tr;
-    float C[3];
-    float stop_T;
-    float Cf[3];          // GRAD only
-    float g[3];           // GRAD only
-    float* grad;          // GRAD only: F32 leaf records, 192 floats per slot
-    float4* rec;          // REC: this ray's segment records
-    int rec_cap;
-    int rec_n;
-    float pk[3];          // this lane's coefficients of the leaf being shaded
+    RowSlots sl;
+    int lane;             // 0 .. 15
+    float Cf[3];
+    float g[3];
+    float* grad;          // F32 leaf records, 192 floats per slot
 
-    // Load this lane's three coefficients of a leaf (all three before the
-    // density sum decides whether the colour is needed: one memory round trip
-    // per segment instead of two).
-    __device__ inline void prefetch(int leaf)
+    // This lane's coefficients of a leaf; slots past 165 read the record's zero padding.
+    __device__ inline void load(int leaf, float* pk) const
     {
         constexpr int kRecFloats = 4 * Pack<FPO_F32>::R;
         const float* rc = reinterpret_cast<const float*>(T.recs) + (int64_t)leaf * kRecFloats + lane;
-        pk[0] = rc[0];
-        pk[1] = rc[kWave];
-        pk[2] = sl.c[2] >= 0 ? rc[2 * kWave] : 0.0f;
+#pragma unroll
+        for (int s = 0; s < kRowSlots; ++s) pk[s] = rc[kRow * s];
     }
 
-    // One segment entered with transmittance Tr_in after colour A (updated in
-    // place), its coefficients loaded by prefetch(leaf).  Returns false for a
-    // transparent segment (nothing to do); otherwise e = exp(-sigma delta).
-    __device__ inline bool shade(int leaf, float delta, float Tr_in, float* A, float& e)
+    // One segment entered with transmittance Tr_in after colour A, with its
+    // leaf's coefficients from load().
+    __device__ inline void shade(int leaf, const float* pk, float delta, float Tr_in, float* A) const
     {
         constexpr int kRecFloats = 4 * Pack<FPO_F32>::R;
-        const float k[3] = {pk[0], pk[1], pk[2]};
-        const float sraw = wave_sum(sl.c[0] == -1 ? sl.w[0] * k[0] : 0.0f);
-        const float sig = T.sigma_scale * fmaxf(sraw, 0.0f);
-        if (!(sig * delta > 0.0f)) return false;   // transparent: contributes nothing
-        float h[3] = {0.0f, 0.0f, 0.0f};
+        float h[4] = {0.0f, 0.0f, 0.0f, 0.0f};     // density, channels
 #pragma unroll
-        for (int s = 0; s < 3; ++s)
+        for (int s = 0; s < kRowSlots; ++s) {
+            const int f = RowSlots::feeds(lane, s);
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) h[ch] = fmaf(sl.c[s] == ch ? sl.w[s] : 0.0f, k[s], h[ch]);
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) h[ch] = wave_sum(h[ch]);
-        e = __expf(-sig * delta);
-        const float w = Tr_in * (1.0f - e);
-        if constexpr (!GRAD) {
-            if constexpr (REC) {
-                if (lane == 0 && rec_n < rec_cap) {
-                    rec[2 * rec_n] = make_float4(__int_as_float(leaf), delta, Tr_in, A[0]);
-                    rec[2 * rec_n + 1] = make_float4(A[1], A[2], 0.0f, 0.0f);
-                }
-                ++rec_n;
-            }
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) A[ch] = fmaf(w, sigmoidf_(h[ch]), A[ch]);
-        } else {
-            const float T_next = Tr_in * e;
-            float dsig = 0.0f, dh[3];
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                const float col = sigmoidf_(h[ch]);
-                A[ch] = fmaf(w, col, A[ch]);
-                dsig = fmaf(g[ch], T_next * col - (Cf[ch] - A[ch]), dsig);
-                dh[ch] = g[ch] * w * col * (1.0f - col);
-            }
-            dsig *= delta * T.sigma_scale;    // sigma_raw > 0 here
-            float* gr = grad + (int64_t)leaf * kRecFloats + lane;
-#pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                const int ch = sl.c[s];
-                if (ch == -2) continue;
-                const float dv = ch == -1 ? dsig : ch == 0 ? dh[0] : ch == 1 ? dh[1] : dh[2];
-                unsafeAtomicAdd(gr + kWave * s, dv * sl.w[s]);
-            }
+            for (int ch = 0; ch < 4; ++ch) h[ch] = f == ch - 1 ? fmaf(sl.w[s], pk[s], h[ch]) : h[ch];
         }
-        return true;
-    }
-
-    __device__ inline bool segment(int leaf, float t0, float t1)
-    {
-        float e;
-        if (!shade(leaf, t1 - t0, Tr, C, e)) return false;
-        Tr *= e;
-        return Tr < stop_T;
+        const float sraw = row_sum(h[0]);
+        const float sig = T.sigma_scale * fmaxf(sraw, 0.0f);
+        if (!(sig * delta > 0.0f)) return;         // transparent: contributes nothing
+#pragma unroll
+        for (int ch = 1; ch < 4; ++ch) h[ch] = row_sum(h[ch]);
+        const float e = __expf(-sig * delta);
+        const float w = Tr_in * (1.0f - e);
+        const float T_next = Tr_in * e;
+        float dsig = 0.0f, dh[3];
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            const float col = sigmoidf_(h[1 + ch]);
+            A[ch] = fmaf(w, col, A[ch]);
+            dsig = fmaf(g[ch], T_next * col - (Cf[ch] - A[ch]), dsig);
+            dh[ch] = g[ch] * w * col * (1.0f - col);
+        }
+        dsig *= delta * T.sigma_scale;    // sigma_raw > 0 here
+        float* gr = grad + (int64_t)leaf * kRecFloats + lane;
+#pragma unroll
+        for (int s = 0; s < kRowSlots; ++s) {
+            const int f = RowSlots::feeds(lane, s);
+            if (f == -2) continue;
+            const float dv = f == -1 ? dsig : f == 0 ? dh[0] : f == 1 ? dh[1] : dh[2];
+            unsafeAtomicAdd(gr + kRow * s, dv * sl.w[s]);
+        }
     }
 };
-
-template <bool GRAD, bool REC>
-__device__ inline void prefetch_leaf(WaveShade<GRAD, REC>& v, int leaf)
-{
-    v.prefetch(leaf);
-}
 
 }  // namespace dev
 }  // namespace fpo

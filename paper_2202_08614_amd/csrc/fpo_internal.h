@@ -58,6 +58,11 @@ struct RecordLayout {
 };
 fpo_status record_layout(const fpo_render_opts* opts, int64_t n_rays, RecordLayout& out);
 
+// Lanes per ray of an F32 Fourier-mode batch of n rays where segment records
+// are, or could be, kept: the forward (up to FPO_RECORD_MAX_RAYS rays) and the
+// backward have to cut the rays alike (collect_records).
+inline int record_parts(int max_depth, int64_t n) { return n <= (32ll << max_depth) ? 32 : 16; }
+
 // Camera frame in FP64, rounded to FP32: eye, unit forward, right * tan_x, up' * tan_y.
 fpo_status camera_frame(const fpo_camera& cam, float out[12]);
 

@@ -209,14 +209,7 @@ __global__ __launch_bounds__(kBlock) void skip_scan_kernel(SkipLaunch a)
 // skip pre-pass left in a.skip.  BUF (snapshot modes, records within 4 GiB):
 // snapshot reads through a buffer resource, and at most 64 VGPRs.
 //
-// PARTS > 1: that many lanes share a ray, each walking an equal part of its
-// chord from transmittance 1; the parts' colours and transmittances are then
-// composed front to back, C = C_0 + T_0 (C_1 + T_1 (...)).  A launch of few
-// waves lasts as long as its longest rays (each step waits for two or three
-// dependent reads, about 2 us), and this cuts them.  The stop rule stays the
-// walk's: the part in which the ray's transmittance falls below stop_T is
-// walked again from the transmittance it is entered with, the later ones are
-// dropped.
+// PARTS > 1: that many lanes share a ray (walk_parts).
 template <int MODE, bool SKIP, int N1 = FPO_N_SIGMA, int N2 = FPO_N_SH_FOURIER, bool BUF = false, int PARTS = 1,
           int WAVES = cam_waves(MODE)>
 __global__ __launch_bounds__(64 * WAVES, BUF && PARTS == 1 ? 32 / WAVES : 1) void render_cam_kernel(CamLaunch a)
@@ -268,53 +261,10 @@ __global__ __launch_bounds__(64 * WAVES, BUF && PARTS == 1 ? 32 / WAVES : 1) voi
     if constexpr (SKIP) hit = setup_ray(cam.frame[0], cam.frame[1], cam.frame[2], dx, dy, dz, r);
     else hit = setup_ray_in(a.tree.box_lo, a.tree.box_hi, cam.frame[0], cam.frame[1], cam.frame[2], dx, dy, dz, r);
     if constexpr (PARTS > 1) {
-        NoStop ns;
-        const float t0 = r.t_len * ((float)part * (1.0f / PARTS));
-        const float t1 = part == PARTS - 1 ? __builtin_inff() : r.t_len * ((float)(part + 1) * (1.0f / PARTS));
         if (hit) sh9(r.d[0], r.d[1], r.d[2], sh.Y);
-        float Tin = 1.0f;                     // transmittance in front of this part
-        float Tout = 1.0f;                    // and behind it
-        bool alive = true;
-        // pass 0: every part from transmittance 1; pass 1: the part in which the ray stops
-        bool go = hit;
-        for (int pass = 0; pass < 2; ++pass) {
-            if (go) walk<(MODE >= 16), kThreads, true>(a.tree, r, s_stack + threadIdx.x, sh, t1, ns, t0);
-            if (pass == 1) break;
-#pragma unroll
-            for (int q = 0; q < PARTS - 1; ++q) {
-                const float Tq = __shfl(sh.Tr, q * kPix + lp, 64);
-                if (q < part) Tin *= Tq;
-            }
-            alive = !(Tin < a.stop_T);
-            Tout = Tin * sh.Tr;
-            go = hit && alive && part > 0 && Tout < a.stop_T;
-            if (go) {
-                sh.Tr = Tin;
-                sh.C[0] = sh.C[1] = sh.C[2] = 0.0f;
-            } else {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) sh.C[c] *= Tin;
-            }
-            if (!__any(go)) break;
-        }
-        if (go) Tout = sh.Tr;
-        float C[3] = {0.0f, 0.0f, 0.0f}, Tr = 1.0f;
-#pragma unroll
-        for (int q = 0; q < PARTS; ++q) {
-            const int src = q * kPix + lp;
-            const int on = __shfl((int)alive, src, 64);
-            const float Tq = __shfl(Tout, src, 64);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float Cq = __shfl(sh.C[c], src, 64);
-                C[c] = on ? C[c] + Cq : C[c];
-            }
-            Tr = on ? Tq : Tr;
-        }
+        const PartFront f = walk_parts<PARTS, (MODE >= 16), kThreads>(a.tree, r, s_stack + threadIdx.x, sh, hit, part, lp);
+        compose_parts<PARTS>(f, sh, part, lp);
         if (part != 0) return;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) sh.C[c] = C[c];
-        sh.Tr = Tr;
     } else if (hit) {
         sh9(r.d[0], r.d[1], r.d[2], sh.Y);
         if constexpr (!SKIP) {
@@ -365,73 +315,80 @@ struct RaysLaunch {
     int32_t rec_cap;
 };
 
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void render_rays_kernel(RaysLaunch a)
+// A batch of rays, PARTS lanes each (walk_parts).
+template <int MODE, int PARTS>
+__global__ __launch_bounds__(kWave) void render_rays_kernel(RaysLaunch a)
 {
-    __shared__ int s_stack[kStackLevels * kBlock];
-    const int64_t r_id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r_id >= a.n) return;
-    int ti = a.t_idx[r_id];
-    ti = min(max(ti, 0), a.n_t - 1);
+    constexpr int kSlots = kWave / PARTS;
+    __shared__ int s_stack[kStackLevels * kWave];
+    const int part = threadIdx.x / kSlots, slot = threadIdx.x % kSlots;
+    const int64_t r_id = (int64_t)blockIdx.x * kSlots + slot;
+    if (r_id >= a.n) return;                  // all lanes of a ray together
+    const int ti = min(max(a.t_idx[r_id], 0), a.n_t - 1);
     float b[FPO_BASIS_STRIDE];
-    const float4* brow = reinterpret_cast<const float4*>(a.basis + (int64_t)ti * FPO_BASIS_STRIDE);
-#pragma unroll
-    for (int i = 0; i < FPO_BASIS_STRIDE / 4; ++i) {
-        const float4 v = brow[i];
-        b[4 * i] = v.x; b[4 * i + 1] = v.y; b[4 * i + 2] = v.z; b[4 * i + 3] = v.w;
-    }
+    load_basis(a.basis, ti, b);
     const void* snap = a.snap;
     if constexpr (MODE >= 16) {
         const size_t rec = (MODE - 16) == FPO_F32 ? 128 : 64;
         snap = static_cast<const char*>(a.snap) + (size_t)ti * (size_t)a.snap_stride * rec;
     }
     Shade<MODE> sh{a.tree, b, snap};
-    sh.Tr = 1.0f;
-    sh.C[0] = sh.C[1] = sh.C[2] = 0.0f;
     sh.stop_T = a.stop_T;
+    sh.restart(1.0f);
     Ray r;
-    if (setup_ray_in(a.tree.box_lo, a.tree.box_hi, a.o[3 * r_id], a.o[3 * r_id + 1], a.o[3 * r_id + 2],
-                  a.d[3 * r_id], a.d[3 * r_id + 1], a.d[3 * r_id + 2], r)) {
-        sh9(r.d[0], r.d[1], r.d[2], sh.Y);
-        walk(a.tree, r, s_stack + threadIdx.x, sh);
+    const bool hit = setup_ray_in(a.tree.box_lo, a.tree.box_hi, a.o[3 * r_id], a.o[3 * r_id + 1], a.o[3 * r_id + 2],
+                                  a.d[3 * r_id], a.d[3 * r_id + 1], a.d[3 * r_id + 2], r);
+    if (hit) sh9(r.d[0], r.d[1], r.d[2], sh.Y);
+    if constexpr (PARTS > 1) {
+        const PartFront f = walk_parts<PARTS, true, kWave>(a.tree, r, s_stack + threadIdx.x, sh, hit, part, slot);
+        compose_parts<PARTS>(f, sh, part, slot);
+        if (part != 0) return;
+    } else if (hit) {
+        walk<false, kWave>(a.tree, r, s_stack + threadIdx.x, sh);
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) a.rgb[r_id * 3 + c] = fmaf(sh.Tr, a.bg[c], sh.C[c]);
     if (a.Tout) a.Tout[r_id] = sh.Tr;
 }
 
-// F32 Fourier-mode render of a small ray batch, one ray per wave.  REC: also
-// write each ray's segment records (FPO_RAYS_RECORD).
-template <bool REC>
-__global__ __launch_bounds__(kBlock, REC ? 8 : 1) void render_rays_wave_kernel(RaysLaunch a)
+// The F32 Fourier-mode batch with each ray's segment records (FPO_RAYS_RECORD,
+// collect_records).
+template <int PARTS>
+__global__ __launch_bounds__(kWave) void render_rays_record_kernel(RaysLaunch a)
 {
-    __shared__ int s_stack[kStackLevels * kBlock];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r_id = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-    if (r_id >= a.n) return;
+    constexpr int kSlots = kWave / PARTS;
+    __shared__ int s_stack[kStackLevels * kWave];
+    __shared__ __align__(16) float4 s_rec[kRecStage];
+    const int part = threadIdx.x / kSlots, slot = threadIdx.x % kSlots;
+    const int64_t r_id = (int64_t)blockIdx.x * kSlots + slot;
+    if (r_id >= a.n) return;                  // all lanes of a ray together
     const int ti = min(max(a.t_idx[r_id], 0), a.n_t - 1);
-    WaveShade<false, REC> sh{a.tree};
-    sh.lane = lane;
-    sh.Tr = 1.0f;
-    sh.C[0] = sh.C[1] = sh.C[2] = 0.0f;
-    sh.stop_T = a.stop_T;
-    if constexpr (REC) {
-        sh.rec = a.rec + r_id * a.rec_cap * 2;
-        sh.rec_cap = a.rec_cap;
-    }
+    float b[FPO_BASIS_STRIDE];
+    load_basis(a.basis, ti, b);
+    RecShade sh{{a.tree, b, nullptr}};
     Ray r;
-    if (setup_ray_in(a.tree.box_lo, a.tree.box_hi, a.o[3 * r_id], a.o[3 * r_id + 1], a.o[3 * r_id + 2],
-                  a.d[3 * r_id], a.d[3 * r_id + 1], a.d[3 * r_id + 2], r)) {
-        float Y[FPO_N_SH];
-        sh9(r.d[0], r.d[1], r.d[2], Y);
-        sh.sl.init(lane, a.basis + (int64_t)ti * FPO_BASIS_STRIDE, Y);
-        walk<true>(a.tree, r, s_stack + threadIdx.x, sh);
-    }
-    if (lane == 0) {
+    const bool hit = setup_ray_in(a.tree.box_lo, a.tree.box_hi, a.o[3 * r_id], a.o[3 * r_id + 1], a.o[3 * r_id + 2],
+                                  a.d[3 * r_id], a.d[3 * r_id + 1], a.d[3 * r_id + 2], r);
+    const PartRecords pr = collect_records<PARTS>(a.tree, r, s_stack + threadIdx.x, s_rec + threadIdx.x, sh, hit,
+                                                  a.stop_T, part, slot);
+    compose_parts<PARTS>(pr.f, sh, part, slot);
+    if (part == 0) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) a.rgb[r_id * 3 + c] = fmaf(sh.Tr, a.bg[c], sh.C[c]);
         if (a.Tout) a.Tout[r_id] = sh.Tr;
-        if constexpr (REC) a.rec_count[r_id] = sh.rec_n <= a.rec_cap ? sh.rec_n : -1;
+        a.rec_count[r_id] = pr.total <= a.rec_cap ? pr.total : -1;
+    }
+    if (pr.total > a.rec_cap) return;
+    float4* out = a.rec + (r_id * a.rec_cap + pr.first) * 2;
+    for (int k0 = 0; k0 < pr.mine; k0 += kLaneRecs) {
+        if (k0 > 0) restage<PARTS>(a.tree, r, s_stack + threadIdx.x, sh, pr, part, k0);
+        const int m = min(pr.mine - k0, kLaneRecs);
+        for (int k = 0; k < m; ++k) {
+            float4 x0 = sh.stage[128 * k], x1 = sh.stage[128 * k + 64];
+            pr.finish(x0, x1);
+            out[2 * (k0 + k)] = x0;
+            out[2 * (k0 + k) + 1] = x1;
+        }
     }
 }
 
@@ -937,10 +894,28 @@ extern "C" fpo_status fpo_render_noalloc(const fpo_tree_view* tree, const fpo_ca
     return render_impl(tree, cams, n_cams, &o, rgb_out, T_out, stream, per_launch);
 }
 
-template <int MODE>
-static void launch_rays(const dev::RaysLaunch& a, int64_t grid, hipStream_t s)
+// Lanes per ray of a batch of n rays (see ray_parts; batch rays seldom miss the
+// scene, and share no leaves).  Measured from F32 coefficients at depths 7 (100 k
+// leaves) / 9 (2 M), in us for 32, 16 and 1 lanes: 3001 rays 31 39 152 / 62 97
+// 513, 8192 rays 52 55 197 / 81 123 602, 60 k rays - 239 254 / - 413 879, 120 k
+// rays - 449 299 / - 741 1002; from F32 snapshots 5000 rays 23 30 108 / 45 70
+// 304, 60 k rays 139 87 157 / 174 148 519, 250 k rays 519 292 194 / 651 499 671.
+// One ray per wave, which served up to 32768 rays from F32 coefficients before,
+// took 74 / 220 us for 3001 rays and 100 / 241 us for 8192.
+static int batch_parts(int mode, int max_depth, int64_t n)
 {
-    hipLaunchKernelGGL(dev::render_rays_kernel<MODE>, dim3((unsigned)grid), dim3(dev::kBlock), 0, s, a);
+    if (mode == FPO_F32 && n <= FPO_RECORD_MAX_RAYS) return record_parts(max_depth, n);
+    if (n <= (64ll << max_depth)) return 32;
+    return n <= ((mode >= 16 ? 768ll : 384ll) << max_depth) ? 16 : 1;
+}
+
+template <int MODE>
+static void launch_rays(const dev::RaysLaunch& a, int parts, hipStream_t s)
+{
+    const dim3 grid((unsigned)((a.n * parts + dev::kWave - 1) / dev::kWave)), block(dev::kWave);
+    if (parts == 32) hipLaunchKernelGGL((dev::render_rays_kernel<MODE, 32>), grid, block, 0, s, a);
+    else if (parts == 16) hipLaunchKernelGGL((dev::render_rays_kernel<MODE, 16>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((dev::render_rays_kernel<MODE, 1>), grid, block, 0, s, a);
 }
 
 extern "C" fpo_status fpo_render_rays(const fpo_tree_view* tree, const float* o, const float* d,
@@ -956,7 +931,7 @@ extern "C" fpo_status fpo_render_rays(const fpo_tree_view* tree, const float* o,
     if (n_rays == 0) return FPO_OK;
     RecordLayout rl;
     if (record) {
-        if (mode_of(tree, opts) != FPO_F32 || n_rays > dev::kWaveRayBatch)
+        if (mode_of(tree, opts) != FPO_F32 || n_rays > FPO_RECORD_MAX_RAYS)
             return fail(FPO_E_UNSUPPORTED, "FPO_RAYS_RECORD needs F32 Fourier mode and at most 32768 rays");
         if ((st = record_layout(opts, n_rays, rl)) != FPO_OK) return st;
     }
@@ -977,23 +952,21 @@ extern "C" fpo_status fpo_render_rays(const fpo_tree_view* tree, const float* o,
         a.rec = reinterpret_cast<float4*>(rl.records);
         a.rec_cap = rl.cap;
     }
-    const int64_t grid = (n_rays + dev::kBlock - 1) / dev::kBlock;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int mode = mode_of(tree, opts);
-    if (mode == FPO_F32 && n_rays <= dev::kWaveRayBatch) {
-        const int64_t wgrid = (n_rays + dev::kBlock / dev::kWave - 1) / (dev::kBlock / dev::kWave);
-        if (record)
-            hipLaunchKernelGGL(dev::render_rays_wave_kernel<true>, dim3((unsigned)wgrid), dim3(dev::kBlock), 0, s, a);
-        else
-            hipLaunchKernelGGL(dev::render_rays_wave_kernel<false>, dim3((unsigned)wgrid), dim3(dev::kBlock), 0, s, a);
+    const int parts = batch_parts(mode, tree->max_depth, n_rays);
+    if (record) {
+        const dim3 grid((unsigned)((n_rays * parts + dev::kWave - 1) / dev::kWave)), block(dev::kWave);
+        if (parts == 32) hipLaunchKernelGGL(dev::render_rays_record_kernel<32>, grid, block, 0, s, a);
+        else hipLaunchKernelGGL(dev::render_rays_record_kernel<16>, grid, block, 0, s, a);
         return launch_status("fpo_render_rays");
     }
     switch (mode) {
-        case FPO_F32: launch_rays<FPO_F32>(a, grid, s); break;
-        case FPO_BF16: launch_rays<FPO_BF16>(a, grid, s); break;
-        case FPO_FP8_E4M3: launch_rays<FPO_FP8_E4M3>(a, grid, s); break;
-        case dev::kSnapF32: launch_rays<dev::kSnapF32>(a, grid, s); break;
-        case dev::kSnapBF16: launch_rays<dev::kSnapBF16>(a, grid, s); break;
+        case FPO_F32: launch_rays<FPO_F32>(a, parts, s); break;
+        case FPO_BF16: launch_rays<FPO_BF16>(a, parts, s); break;
+        case FPO_FP8_E4M3: launch_rays<FPO_FP8_E4M3>(a, parts, s); break;
+        case dev::kSnapF32: launch_rays<dev::kSnapF32>(a, parts, s); break;
+        case dev::kSnapBF16: launch_rays<dev::kSnapBF16>(a, parts, s); break;
         default: return fail(FPO_E_INVALID, "unknown render mode");
     }
     return launch_status("fpo_render_rays");

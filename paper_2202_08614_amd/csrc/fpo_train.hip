@@ -2,9 +2,8 @@
 // render into the leaf Fourier coefficients, the L2 photometric loss of
 // Eq. 13 and a fused Adam update over the coefficient planes.
 //
-// Backward: per ray, the forward walk is recomputed, or, when the forward
-// recorded its segments (FPO_RAYS_RECORD), each recorded segment is taken on
-// its own; besides the records, the only forward state used is the ray's
+// Backward: each segment of positive optical depth is taken on its own, as the
+// forward recorded it (FPO_RAYS_RECORD) or as walking the ray again gives it; besides the records, the only forward state used is the ray's
 // final colour.  Walking
 // front to back with transmittance T_i and accumulated colour A_i, the
 // suffix R_i = C - A_i gives
@@ -13,10 +12,9 @@
 // and through Eq. 7 / Eq. 9 and the SH basis of Eq. 1
 //     dL/dk^sigma_q     = s [sigma_raw > 0] dL/dsigma_i b_q,
 //     dL/dk^z_{c,j,i}   = dL/dh_{i,c} Y_j b_i.
-// One wave per ray (or, from records, per segment): each lane owns up to three
-// of a leaf's 166 coefficients, so every sample's gradients go out as three
-// coalesced FP32 atomic adds into records laid out like the F32 coefficient
-// store.
+// 16 lanes per segment: each lane owns up to eleven of a leaf's 166
+// coefficients, so every sample's gradients go out as FP32 atomic adds over 64
+// consecutive bytes each, into records laid out like the F32 coefficient store.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -47,63 +45,130 @@ struct BackwardLaunch {
     int32_t rec_cap;
 };
 
-// Waves per ray when the forward recorded its segments.
+// Rows of 16 lanes per ray when the forward recorded its segments.
 constexpr int kRecGroups = 8;
 
-// The backward, one ray per wave.
-__global__ __launch_bounds__(kBlock) void render_backward_wave_kernel(BackwardLaunch a)
+// The backward without records, 64 / PARTS rays per wave: the wave collects
+// its rays' records as the recording forward does (collect_records); then each
+// row of 16 lanes works through records of one ray, the next one's
+// coefficients on their way.  With records: only the rays that had more than
+// fitted.
+template <int PARTS>
+__global__ __launch_bounds__(kWave) void render_backward_walk_kernel(BackwardLaunch a)
 {
-    __shared__ int s_stack[kStackLevels * kBlock];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r_id = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-    if (r_id >= a.n) return;
-    const int ti = min(max(a.t_idx[r_id], 0), a.n_t - 1);
-    WaveShade<true> sh{a.tree};
-    sh.lane = lane;
-    sh.Tr = 1.0f;
-    sh.stop_T = a.stop_T;
-    sh.grad = a.grad;
+    constexpr int kSlots = kWave / PARTS;
+    constexpr int kRowsPerRay = kWave / kRow / kSlots;
+    __shared__ int s_stack[kStackLevels * kWave];
+    __shared__ __align__(16) float4 s_rec[kRecStage];
+    __shared__ uint16_t s_list[kSlots][PARTS * kLaneRecs];
+    const int lane = threadIdx.x;
+    const int part = lane / kSlots, slot = lane % kSlots;
+    const int64_t r_id = (int64_t)blockIdx.x * kSlots + slot;
+    const int64_t at = min(r_id, a.n - 1);
+    bool live = r_id < a.n;
+    if (a.rec_count && live) {
+        const int cnt = a.rec_count[at];
+        live = cnt < 0 || cnt > a.rec_cap;            // not a count the forward writes: walk the ray
+    }
+    if (!__any(live)) return;
+    float g[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) g[c] = a.grad_rgb[at * 3 + c];
+    live = live && !(g[0] == 0.0f && g[1] == 0.0f && g[2] == 0.0f);
+    const int ti = min(max(a.t_idx[at], 0), a.n_t - 1);
+    Ray r;
+    const bool hit = live && setup_ray_in(a.tree.box_lo, a.tree.box_hi, a.o[3 * at], a.o[3 * at + 1], a.o[3 * at + 2],
+                                          a.d[3 * at], a.d[3 * at + 1], a.d[3 * at + 2], r);
+    if (!__any(hit)) return;
+    if (!hit) {
+        r.t_len = 0.0f;
+        r.d[0] = r.d[1] = r.d[2] = 0.0f;
+    }
+    float b[FPO_BASIS_STRIDE];
+    load_basis(a.basis, ti, b);
+    RecShade sh{{a.tree, b, nullptr}};
+    const PartRecords pr = collect_records<PARTS>(a.tree, r, s_stack + lane, s_rec + lane, sh, hit, a.stop_T, part, slot);
+    // this row's ray
+    const int rs = (lane / kRow) % kSlots;            // its slot; lane rs holds the ray's part 0
+    const int64_t ra = min((int64_t)blockIdx.x * kSlots + rs, a.n - 1);
+    RowGrad wg{a.tree};
+    wg.lane = lane % kRow;
+    wg.grad = a.grad;
+    {
+        float Y[FPO_N_SH];
+        sh9(__shfl(r.d[0], rs, kWave), __shfl(r.d[1], rs, kWave), __shfl(r.d[2], rs, kWave), Y);
+        wg.sl.init(wg.lane, a.basis + (int64_t)__shfl(ti, rs, kWave) * FPO_BASIS_STRIDE, Y);
+    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        sh.C[c] = 0.0f;
-        sh.Cf[c] = a.rgb_fwd[r_id * 3 + c];
-        sh.g[c] = a.grad_rgb[r_id * 3 + c];
+        wg.Cf[c] = a.rgb_fwd[ra * 3 + c];
+        wg.g[c] = __shfl(g[c], rs, kWave);
     }
-    if (sh.g[0] == 0.0f && sh.g[1] == 0.0f && sh.g[2] == 0.0f) return;
-    Ray r;
-    if (setup_ray_in(a.tree.box_lo, a.tree.box_hi, a.o[3 * r_id], a.o[3 * r_id + 1], a.o[3 * r_id + 2],
-                  a.d[3 * r_id], a.d[3 * r_id + 1], a.d[3 * r_id + 2], r)) {
-        float Y[FPO_N_SH];
-        sh9(r.d[0], r.d[1], r.d[2], Y);
-        sh.sl.init(lane, a.basis + (int64_t)ti * FPO_BASIS_STRIDE, Y);
-        walk<true>(a.tree, r, s_stack + threadIdx.x, sh);
+    for (int k0 = 0; __any(pr.mine > k0); k0 += kLaneRecs) {
+        if (k0 > 0 && pr.mine > k0) restage<PARTS>(a.tree, r, s_stack + lane, sh, pr, part, k0);
+        const int m = min(max(pr.mine - k0, 0), kLaneRecs);
+        // each ray's staged records as one list
+        int end = m;
+#pragma unroll
+        for (int off = kSlots; off < kWave; off <<= 1) {
+            const int v = __shfl_up(end, off, kWave);
+            if (lane >= off) end += v;
+        }
+        const int count = __shfl(end, kWave - kSlots + rs, kWave);
+        for (int k = 0; k < m; ++k) {
+            pr.finish(sh.stage[128 * k], sh.stage[128 * k + 64]);
+            s_list[slot][end - m + k] = (uint16_t)(128 * k + lane);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        float nk[kRowSlots];
+        float4 x0, x1;
+        int i = lane / kRow / kSlots;
+        if (i < count) {
+            x0 = s_rec[s_list[rs][i]];
+            x1 = s_rec[s_list[rs][i] + 64];
+            wg.load(__float_as_int(x0.x), nk);
+        }
+        for (; i < count; i += kRowsPerRay) {
+            float pk[kRowSlots];
+#pragma unroll
+            for (int s = 0; s < kRowSlots; ++s) pk[s] = nk[s];
+            const int leaf = __float_as_int(x0.x);
+            const float delta = x0.y, Tr = x0.z;
+            float A[3] = {x0.w, x1.x, x1.y};
+            if (i + kRowsPerRay < count) {
+                x0 = s_rec[s_list[rs][i + kRowsPerRay]];
+                x1 = s_rec[s_list[rs][i + kRowsPerRay] + 64];
+                wg.load(__float_as_int(x0.x), nk);
+            }
+            wg.shade(leaf, pk, delta, Tr, A);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 }
 
-// The backward from segment records: wave (r, q) takes ray r's recorded
+// The backward from segment records: row (r, q) takes ray r's recorded
 // segments q, q + 8, ...; each already carries the transmittance and the
 // colour accumulated in front of it, so no walk is needed and the segments of
-// one ray run side by side.  A ray whose records overflowed is walked again by
-// its wave q = 0.
+// one ray run side by side.  Rays whose records overflowed are left to
+// render_backward_walk_kernel.
 __global__ __launch_bounds__(kBlock) void render_backward_rec_kernel(BackwardLaunch a)
 {
-    __shared__ int s_stack[kStackLevels * kBlock];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t w_id = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    const int lane = threadIdx.x % kRow;
+    const int64_t w_id = (int64_t)blockIdx.x * (kBlock / kRow) + threadIdx.x / kRow;
     const int64_t r_id = w_id / kRecGroups;
     const int q = (int)(w_id - r_id * kRecGroups);
     if (r_id >= a.n) return;
-    int cnt = a.rec_count[r_id];
-    if (cnt > a.rec_cap) cnt = -1;       // not a count the forward writes: walk the ray instead
-    if (cnt < 0 ? q != 0 : q >= cnt) return;
-    WaveShade<true> sh{a.tree};
+    const int cnt = a.rec_count[r_id];
+    if (q >= cnt || cnt > a.rec_cap) return;
+    RowGrad sh{a.tree};
     sh.lane = lane;
-    sh.Tr = 1.0f;
-    sh.stop_T = a.stop_T;
     sh.grad = a.grad;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        sh.C[c] = 0.0f;
         sh.Cf[c] = a.rgb_fwd[r_id * 3 + c];
         sh.g[c] = a.grad_rgb[r_id * 3 + c];
     }
@@ -116,10 +181,6 @@ __global__ __launch_bounds__(kBlock) void render_backward_rec_kernel(BackwardLau
     float Y[FPO_N_SH];
     sh9(r.d[0], r.d[1], r.d[2], Y);
     sh.sl.init(lane, a.basis + (int64_t)ti * FPO_BASIS_STRIDE, Y);
-    if (cnt < 0) {
-        walk<true>(a.tree, r, s_stack + threadIdx.x, sh);
-        return;
-    }
     const float4* rr = a.rec + r_id * a.rec_cap * 2;
     for (int i = q; i < cnt; i += kRecGroups) {
         const float4 x0 = rr[2 * i];
@@ -127,9 +188,9 @@ __global__ __launch_bounds__(kBlock) void render_backward_rec_kernel(BackwardLau
         const int leaf = __float_as_int(x0.x);
         if (leaf < 0 || leaf >= a.tree.n_leaves) continue;   // only the forward's leaves are read
         float A[3] = {x0.w, x1.x, x1.y};
-        float e;
-        sh.prefetch(leaf);
-        sh.shade(leaf, x0.y, x0.z, A, e);
+        float pk[kRowSlots];
+        sh.load(leaf, pk);
+        sh.shade(leaf, pk, x0.y, x0.z, A);
     }
 }
 
@@ -292,23 +353,24 @@ extern "C" fpo_status fpo_render_backward(const fpo_tree_view* tree, const float
     a.o = o; a.d = d; a.t_idx = t_idx; a.basis = basis; a.n = n_rays; a.n_t = n_t;
     a.rgb_fwd = rgb_fwd; a.grad_rgb = grad_rgb; a.grad = grad_coeffs;
     a.stop_T = opts->stop_T;
+    hipStream_t s = static_cast<hipStream_t>(stream);
     if (opts->flags == FPO_RAYS_RECORD) {
-        if (n_rays > dev::kWaveRayBatch)
+        if (n_rays > FPO_RECORD_MAX_RAYS)
             return fail(FPO_E_UNSUPPORTED, "FPO_RAYS_RECORD needs at most 32768 rays");
         RecordLayout rl;
         if ((st = record_layout(opts, n_rays, rl)) != FPO_OK) return st;
         a.rec_count = rl.count;
         a.rec = static_cast<const float4*>(rl.records);
         a.rec_cap = rl.cap;
-        const int64_t waves = n_rays * dev::kRecGroups;
-        const int64_t rgrid = (waves + dev::kBlock / dev::kWave - 1) / (dev::kBlock / dev::kWave);
-        hipLaunchKernelGGL(dev::render_backward_rec_kernel, dim3((unsigned)rgrid), dim3(dev::kBlock), 0,
-                           static_cast<hipStream_t>(stream), a);
-        return launch_status("fpo_render_backward");
+        const int64_t rgrid = (n_rays * dev::kRecGroups + dev::kBlock / dev::kRow - 1) / (dev::kBlock / dev::kRow);
+        hipLaunchKernelGGL(dev::render_backward_rec_kernel, dim3((unsigned)rgrid), dim3(dev::kBlock), 0, s, a);
+        if ((st = launch_status("fpo_render_backward")) != FPO_OK) return st;
     }
-    const int64_t wgrid = (n_rays + dev::kBlock / dev::kWave - 1) / (dev::kBlock / dev::kWave);
-    hipLaunchKernelGGL(dev::render_backward_wave_kernel, dim3((unsigned)wgrid), dim3(dev::kBlock), 0,
-                       static_cast<hipStream_t>(stream), a);
+    // every ray, or those whose records overflowed
+    const int parts = record_parts(tree->max_depth, n_rays);
+    const dim3 grid((unsigned)((n_rays * parts + dev::kWave - 1) / dev::kWave)), block(dev::kWave);
+    if (parts == 32) hipLaunchKernelGGL(dev::render_backward_walk_kernel<32>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(dev::render_backward_walk_kernel<16>, grid, block, 0, s, a);
     return launch_status("fpo_render_backward");
 }
 
