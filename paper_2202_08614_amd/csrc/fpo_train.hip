@@ -234,6 +234,11 @@ __global__ __launch_bounds__(kBlock) void l2_loss_kernel(const float* rgb, const
 // Adam (Kingma and Ba 2015) over n floats; the gradient is cleared after use.
 // c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t).
 // cs: null, or device {c1, c2} written by adam_count_kernel (then c1, c2 are unused).
+// HBM-bound: 16 bytes read and 12 written per parameter.  A gradient that is
+// zero already, as in every record the batch did not reach, is not written
+// again: 600 -> 540 us for 96 M floats (5.0 TB/s).  Leaving out the unchanged
+// padding of p, m and v as well took 575 us: partly written lines cost more
+// than whole ones.
 __global__ __launch_bounds__(kBlock) void adam_kernel(float4* p, float4* g, float4* m, float4* v, int64_t n4,
                                                       float lr, float b1, float b2, float eps, float c1, float c2,
                                                       const float* cs)
@@ -244,9 +249,10 @@ __global__ __launch_bounds__(kBlock) void adam_kernel(float4* p, float4* g, floa
         c1 = cs[0];
         c2 = cs[1];
     }
-    float4 pp = p[i], gg = g[i], mm = m[i], vv = v[i];
+    const float4 gg = g[i];
+    float4 pp = p[i], mm = m[i], vv = v[i];
     float* P = &pp.x;
-    float* G = &gg.x;
+    const float* G = &gg.x;
     float* M = &mm.x;
     float* V = &vv.x;
 #pragma unroll
@@ -260,7 +266,9 @@ __global__ __launch_bounds__(kBlock) void adam_kernel(float4* p, float4* g, floa
     p[i] = pp;
     m[i] = mm;
     v[i] = vv;
-    g[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    // by bits: a negative zero is cleared too
+    if ((__float_as_uint(gg.x) | __float_as_uint(gg.y) | __float_as_uint(gg.z) | __float_as_uint(gg.w)) != 0u)
+        g[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
 // Adam on touched records only: one wave per record of rq float4 (rq <= 64).

@@ -230,6 +230,23 @@ def test_l2_loss_kernel(dev):
     assert np.allclose(grad.cpu().numpy(), 2 * e / n, atol=1e-7)
 
 
+def test_adam_clears_every_gradient(dev):
+    """Zero gradients are not written again; anything else is, by bits."""
+    import torch
+    n = 4096
+    g = torch.zeros(n, device=dev)
+    g[5], g[64], g[1000], g[4095] = -0.0, 1e-45, float("nan"), 2.0
+    p, m, v = torch.ones(n, device=dev), torch.full((n,), 0.5, device=dev), torch.full((n,), 0.25, device=dev)
+    note("adam_step clears")
+    _lib.adam_step(p, g, m, v, 1)
+    torch.cuda.synchronize()
+    assert not bool(g.view(torch.int32).any())
+    same = torch.tensor([i for i in range(n) if i not in (64, 1000, 4095)], device=dev)
+    for a in (p, m, v):
+        assert bool((a[same] == a[0]).all()) and float(a[0]) not in (1.0, 0.5, 0.25)
+    assert bool(torch.isnan(p[1000])) and float(m[4095]) > float(m[0])
+
+
 def test_adam_kernel_matches_reference(dev):
     import torch
     rng = np.random.default_rng(5)
