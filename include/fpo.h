@@ -610,6 +610,22 @@ fpo_status fpo_fusion_observe(const fpo_tree_view* tree, const float* values, co
 fpo_status fpo_fusion_apply(float* values, float* weight, int32_t* count, float* acc, int64_t n_leaves,
                             void* stream);
 
+/* fpo_fusion_observe and fpo_fusion_apply of one view in one call (Sec. 3, Eq.
+ * 3-5): the same update up to FP32 rounding and the order of the sums,
+ * including what earlier observe calls left in acc, which is zero afterwards.
+ * Observations are collected per leaf in `workspace` instead of being added to
+ * acc; if they do not fit, the view is taken through acc.
+ *   values, weight, count  device, as for fpo_fusion_apply (all n_leaves).
+ *   workspace  device, 256-byte aligned; needs no initialisation.  Written by
+ *              the call's device work; calls in flight at once need one each.
+ * fpo_fusion_view_bytes: a workspace that holds the observations of a view of
+ * this size (at most about 2.5 GiB), or 0 where it would be larger.  No device
+ * work. */
+int64_t fpo_fusion_view_bytes(const fpo_tree_view* tree, const fpo_camera* cam);
+fpo_status fpo_fusion_view(const fpo_tree_view* tree, float* values, float* weight, int32_t* count,
+                           const fpo_camera* cam, const fpo_field* field, float tau, float* acc,
+                           void* workspace, int64_t workspace_bytes, void* stream);
+
 /* ---------------------------------------------------------------------- */
 /* Learned proposal (not in the paper)                                      */
 /* ---------------------------------------------------------------------- */

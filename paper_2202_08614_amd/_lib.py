@@ -128,13 +128,16 @@ _SIGS = {
     "fpo_fusion_observe": [ctypes.POINTER(TreeView), _P, ctypes.POINTER(CameraC), ctypes.POINTER(FieldC),
                            ctypes.c_float, _P, _P],
     "fpo_fusion_apply": [_P, _P, _P, _P, _I64, _P],
+    "fpo_fusion_view": [ctypes.POINTER(TreeView), _P, _P, _P, ctypes.POINTER(CameraC), ctypes.POINTER(FieldC),
+                        ctypes.c_float, _P, _P, _I64, _P],
     "fpo_prune_at": [ctypes.POINTER(TreeView), _P, ctypes.c_int, _I64, _I32, _P, _P],
     "fpo_prune_at_sigma": [ctypes.POINTER(TreeView), _P, _I64, _I32, _P, _P],
     "fpo_grandchild_tables": [_P, _I64, _I32, _I64, _P, _P],
     "fpo_coarse_occupancy_at": [_P, _I64, _I32, _P, ctypes.c_int, ctypes.c_float, _P, _P],
 }
 # functions with another return type
-_OTHER = {"fpo_mlp_workspace_floats": ([_I64], ctypes.c_int64),
+_OTHER = {"fpo_fusion_view_bytes": ([ctypes.POINTER(TreeView), ctypes.POINTER(CameraC)], ctypes.c_int64),
+          "fpo_mlp_workspace_floats": ([_I64], ctypes.c_int64),
           "fpo_render_decode_bytes": ([ctypes.POINTER(TreeView), ctypes.POINTER(CameraC), _I32,
                                        ctypes.POINTER(RenderOpts)], ctypes.c_int64)}
 
@@ -808,6 +811,29 @@ def fusion_apply(values, weight, count, acc, n_leaves: int):
     """fpo_fusion_apply over the first n_leaves slots."""
     _check(lib().fpo_fusion_apply(_t_ptr(values), _t_ptr(weight), _t_ptr(count), _t_ptr(acc), int(n_leaves),
                                   _stream()))
+
+
+def fusion_view(tree: DeviceTree, values, weight, count, cam, field, acc, tau: float = 1e-3):
+    """fpo_fusion_view with a workspace for the call (from torch's allocator);
+    fusion_observe and fusion_apply where that is too large, cannot be had, or
+    would be kept by a HIP graph under capture."""
+    import torch
+    tv = tree.view()
+    cs = camera_struct([cam])
+    fs = field_struct(field) if not isinstance(field, FieldC) else field
+    nbytes = lib().fpo_fusion_view_bytes(ctypes.byref(tv), cs)
+    ws = None
+    if nbytes > 0 and not torch.cuda.is_current_stream_capturing():
+        try:
+            ws = torch.empty((nbytes,), dtype=torch.uint8, device=values.device)
+        except torch.OutOfMemoryError:
+            ws = None
+    if ws is None:
+        fusion_observe(tree, values, cam, fs, acc, tau)
+        fusion_apply(values, weight, count, acc, tree.n_leaves)
+        return
+    _check(lib().fpo_fusion_view(ctypes.byref(tv), _t_ptr(values), _t_ptr(weight), _t_ptr(count), cs,
+                                 ctypes.byref(fs), float(tau), _t_ptr(acc), _t_ptr(ws), nbytes, _stream()))
 
 
 # ---------------------------------------------------------------------------
