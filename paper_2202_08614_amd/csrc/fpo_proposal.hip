@@ -215,17 +215,16 @@ __device__ inline float log1p_unit(float u)
     return w == 1.0f ? u : logf(w) * (u / (w - 1.0f));
 }
 
-// LDS of mlp_grad_kernel.  Rows of 68 floats (4 mod 64 banks): 16 lanes along a
-// row times 4 rows one apart, and float4 reads of 16 rows, both spread over all
-// banks.
+// LDS of mlp_grad_kernel.  Activation rows of 68 floats spread the float4 reads
+// of 16 rows over all banks, weight rows of 80 the reads of 16 columns of 4 rows.
 constexpr int kLd = 68;
-constexpr int kEncRows = 88;             // 42 arguments padded to 44, sine and cosine
+constexpr int kLdW1 = 80;
 struct GradLds {
-    float w1[kEncRows][kLd];             // layer 1, rows in encoding order (enc_row)
+    float w1[kMlpPE][kLdW1];
     float w2[kMlpH][kLd];
     float w3[kMlpH * 3];
     float b1[kMlpH], b2[kMlpH], b3[4];
-    float g[kEncRows][kLd];              // encoded inputs of the block's 64 rays
+    float g[kMlpPE][kLd];                // encoded inputs of the block's 64 rays
     float a1[kMlpH][kLd], a2[kMlpH][kLd];
     float d1[kMlpH][kLd], d2[kMlpH][kLd];
     float go[3][kLd];
@@ -233,24 +232,30 @@ struct GradLds {
 };
 static_assert(sizeof(GradLds) <= 160 * 1024, "LDS of a CU");
 
-// Encoding order: row 8 t + 4 q + kq holds argument 4 t + kq (input
-// (4 t + kq) / 6 times 2^((4 t + kq) % 6)), its sine (q = 0) or cosine (q = 1),
-// so that lane group kq of a wave computes both and feeds one MFMA step with
-// each.  Feature of a row (84 and up: padding, arguments 42 and 43).
-__device__ inline int enc_feature(int row) { return 8 * (row >> 3) + 2 * (row & 3) + ((row >> 2) & 1); }
+// What one lane writes to LDS before this is there for the wave's others after it.
+__device__ inline void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Gradient of the batch loss, 64 rays per block and turn, 16 per wave.  All
-// products run on v_mfma_f32_16x16x4f32 (FP32 operands and sums).  Lane (kq, n)
-// works on ray n of its wave; an accumulator tile holds hidden units 16 m + 4
-// kq + r of that ray, which is the operand layout of the next product when its
-// K steps are taken as {16 m + 4 kq + r : kq}, so the layers chain in
-// registers.  Activations and deltas also go to LDS, [unit][ray]; after a
-// barrier wave w forms columns 16 w .. 16 w + 15 of the weight gradients, its
-// K being the block's 64 rays.  Bound by the matrix cores' 412 steps of 32
-// cycles per wave and turn and by the latency around them (one wave per SIMD):
+// products run on v_mfma_f32_16x16x4f32 (FP32 operands and sums), which adds
+// its four products in order, so the forward pass and the deltas, whose K runs
+// over units in order (step s takes 4 s + kq from lane group kq), are the same
+// bits as fused multiply-adds one by one: which units are on does not depend on
+// how the work is cut.  Lane (kq, n) works on ray n of its wave; an accumulator
+// tile holds units 16 m + 4 kq + q of that ray.  Activations and deltas pass
+// through LDS, [unit][ray], from where the next product reads its operand;
+// after a barrier wave w forms columns 16 w .. 16 w + 15 of the weight
+// gradients, its K being the block's 64 rays.  Bound by the latency around the
+// matrix cores' 420 steps of 32 cycles per wave and turn (one wave per SIMD):
 // a 16,384-ray batch is one turn of 256 blocks.  Before, one thread per ray
 // (64 blocks) wrote 344 floats a ray, which a second kernel read back to form
-// the weight gradient in 16 x 16 tiles: 118 + 48 us for that batch.
+// the weight gradient in 16 x 16 tiles: 118 + 48 us for that batch; this takes
+// 25 us, of which about 12 are the rays' work, 5 the partial gradient's stores and the
+// rest the launch and the weights (7 us more while each came as a single float).
 __global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restrict__ P, const float* __restrict__ X,
                                                           const float* __restrict__ Y, const int32_t* __restrict__ idx,
                                                           int64_t n_rays, int64_t n_chunks, float inv_n,
@@ -262,11 +267,33 @@ __global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restric
     const int ln = tid % kWave;
     const int n = ln & 15;
     const int kq = ln >> 4;
-    for (int e = tid; e < kEncRows * kMlpH; e += kBlock) {
-        const int k = enc_feature(e / kMlpH);
-        S.w1[e / kMlpH][e % kMlpH] = k < kMlpPE ? P[kP1 + k * kMlpH + e % kMlpH] : 0.0f;
+    // the weights, every load in flight at once; parameters that are not 16-byte
+    // aligned come as single floats
+    constexpr int kW = kMlpH / 4;            // float4 per row
+    constexpr int kLoads1 = (kMlpPE * kW + kBlock - 1) / kBlock, kLoads2 = kMlpH * kW / kBlock;
+    const bool wide = (reinterpret_cast<uintptr_t>(P) & 15) == 0;
+    auto load4 = [&](int at) {
+        if (wide) return *reinterpret_cast<const f32x4*>(P + at);
+        return f32x4{P[at], P[at + 1], P[at + 2], P[at + 3]};
+    };
+    f32x4 l1[kLoads1], l2[kLoads2];
+#pragma unroll
+    for (int i = 0; i < kLoads1; ++i) {
+        const int e = i * kBlock + tid;
+        l1[i] = e < kMlpPE * kW ? load4(kP1 + e * 4) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    for (int e = tid; e < kMlpH * kMlpH; e += kBlock) S.w2[e / kMlpH][e % kMlpH] = P[kP2 + e];
+#pragma unroll
+    for (int i = 0; i < kLoads2; ++i) l2[i] = load4(kP2 + (i * kBlock + tid) * 4);
+#pragma unroll
+    for (int i = 0; i < kLoads1; ++i) {
+        const int e = i * kBlock + tid;
+        if (e < kMlpPE * kW) *reinterpret_cast<f32x4*>(&S.w1[e / kW][e % kW * 4]) = l1[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kLoads2; ++i) {
+        const int e = i * kBlock + tid;
+        *reinterpret_cast<f32x4*>(&S.w2[e / kW][e % kW * 4]) = l2[i];
+    }
     if (tid < kMlpH * 3) S.w3[tid] = P[kP3 + tid];
     if (tid < kMlpH) {
         S.b1[tid] = P[kP1 + kMlpPE * kMlpH + tid];
@@ -295,6 +322,22 @@ __global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restric
 #pragma unroll
         for (int e = 0; e < 3; ++e) y[e] = live ? Y[row * 3 + e] : 0.0f;
 
+        // encoding: lane group kq takes arguments 4 t + kq, argument i being input
+        // i / 6 times 2^(i % 6), features 2 i (sine) and 2 i + 1 (cosine)
+#pragma unroll
+        for (int t = 0; t < (6 * kMlpIn + 3) / 4; ++t) {
+            float arg = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = 4 * t + q;
+                if (i < 6 * kMlpIn) arg = kq == q ? x[i / 6] * (float)(1 << (i % 6)) : arg;
+            }
+            if (4 * t + kq < 6 * kMlpIn) {
+                S.g[8 * t + 2 * kq][ray] = live ? sinpif(arg) : 0.0f;
+                S.g[8 * t + 2 * kq + 1][ray] = live ? cospif(arg) : 0.0f;
+            }
+        }
+        wave_lds_sync();
         // layer 1
         f32x4 z[4];
 #pragma unroll
@@ -302,64 +345,48 @@ __global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restric
 #pragma unroll
             for (int q = 0; q < 4; ++q) z[m][q] = S.b1[16 * m + 4 * kq + q];
 #pragma unroll
-        for (int t = 0; t < kEncRows / 8; ++t) {
-            float arg = 0.0f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = 4 * t + q;
-                if (i < 6 * kMlpIn) arg = kq == q ? x[i / 6] * (float)(1 << (i % 6)) : arg;
-            }
-            const bool on = live && 4 * t + kq < 6 * kMlpIn;
-            const float sn = on ? sinpif(arg) : 0.0f;
-            const float cs = on ? cospif(arg) : 0.0f;
-            S.g[8 * t + kq][ray] = sn;
-            S.g[8 * t + 4 + kq][ray] = cs;
+        for (int s = 0; s < kMlpPE / 4; ++s) {
+            const float v = S.g[4 * s + kq][ray];
 #pragma unroll
             for (int m = 0; m < 4; ++m)
-                z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w1[8 * t + kq][16 * m + n], sn, z[m], 0, 0, 0);
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-                z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w1[8 * t + 4 + kq][16 * m + n], cs, z[m], 0, 0, 0);
+                z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w1[4 * s + kq][16 * m + n], v, z[m], 0, 0, 0);
         }
         uint32_t on1 = 0, on2 = 0;           // z > 0 of this lane's 16 units
-        f32x4 a[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                a[m][q] = live ? fmaxf(z[m][q], 0.0f) : 0.0f;
                 on1 |= (uint32_t)(z[m][q] > 0.0f) << (4 * m + q);
-                S.a1[16 * m + 4 * kq + q][ray] = a[m][q];
+                S.a1[16 * m + 4 * kq + q][ray] = live ? fmaxf(z[m][q], 0.0f) : 0.0f;
                 z[m][q] = S.b2[16 * m + 4 * kq + q];
             }
+        wave_lds_sync();
         // layer 2
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int s = 0; s < kMlpH / 4; ++s) {
+            const float v = S.a1[4 * s + kq][ray];
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w2[16 * k + 4 * kq + q][16 * m + n], a[k][q], z[m],
-                                                                0, 0, 0);
-        // outputs: each lane's 16 units, then the sum over the ray's 4 lanes
-        float o[3] = {0.0f, 0.0f, 0.0f};
+            for (int m = 0; m < 4; ++m)
+                z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w2[4 * s + kq][16 * m + n], v, z[m], 0, 0, 0);
+        }
 #pragma unroll
         for (int m = 0; m < 4; ++m)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int u = 16 * m + 4 * kq + q;
-                const float v = live ? fmaxf(z[m][q], 0.0f) : 0.0f;
                 on2 |= (uint32_t)(z[m][q] > 0.0f) << (4 * m + q);
-                S.a2[u][ray] = v;
-#pragma unroll
-                for (int e = 0; e < 3; ++e) o[e] = fmaf(v, S.w3[u * 3 + e], o[e]);
+                S.a2[16 * m + 4 * kq + q][ray] = live ? fmaxf(z[m][q], 0.0f) : 0.0f;
             }
+        wave_lds_sync();
+        // outputs: rows 0 .. 2 of a tile, in lane group 0; to all four of the ray's lanes
+        f32x4 oz = {S.b3[0], S.b3[1], S.b3[2], 0.0f};
 #pragma unroll
-        for (int e = 0; e < 3; ++e) {
-            o[e] += __shfl_xor(o[e], 16, kWave);
-            o[e] += __shfl_xor(o[e], 32, kWave);
-            o[e] += S.b3[e];
+        for (int s = 0; s < kMlpH / 4; ++s) {
+            const float w = n < 3 ? S.w3[(4 * s + kq) * 3 + n] : 0.0f;
+            oz = __builtin_amdgcn_mfma_f32_16x16x4f32(w, S.a2[4 * s + kq][ray], oz, 0, 0, 0);
         }
+        float o[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) o[e] = __shfl(oz[e], n, kWave);
         // loss and dL/do: logistic loss on the hit logit, pinball on the sigmoid
         // of the interval outputs for rays that hit
         float loss = fmaxf(o[0], 0.0f) - y[0] * o[0] + log1p_unit(expf(-fabsf(o[0])));
@@ -391,18 +418,17 @@ __global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restric
                 float v = 0.0f;
 #pragma unroll
                 for (int e = 0; e < 3; ++e) v = fmaf(go[e], S.w3[u * 3 + e], v);
-                a[m][q] = ((on2 >> (4 * m + q)) & 1) ? v : 0.0f;
-                S.d2[u][ray] = a[m][q];
+                S.d2[u][ray] = ((on2 >> (4 * m + q)) & 1) ? v : 0.0f;
                 z[m][q] = 0.0f;
             }
+        wave_lds_sync();
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int s = 0; s < kMlpH / 4; ++s) {
+            const float v = S.d2[4 * s + kq][ray];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const f32x4 w = *reinterpret_cast<const f32x4*>(&S.w2[16 * m + n][16 * k + 4 * kq]);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q], a[k][q], z[m], 0, 0, 0);
-            }
+            for (int m = 0; m < 4; ++m)
+                z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(S.w2[16 * m + n][4 * s + kq], v, z[m], 0, 0, 0);
+        }
 #pragma unroll
         for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -423,9 +449,9 @@ __global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restric
                 f32x4 v;
                 if (t < 5) {
                     v = *reinterpret_cast<const f32x4*>(&S.g[16 * t + n][at]);
-                } else {                                 // rows 80 .. 87, then the bias row
-                    v = n == 8 ? f32x4{1.0f, 1.0f, 1.0f, 1.0f} : zero;
-                    if (n < 8) v = *reinterpret_cast<const f32x4*>(&S.g[80 + n][at]);
+                } else {                                 // rows 80 .. 83, then the bias row
+                    v = n == 4 ? f32x4{1.0f, 1.0f, 1.0f, 1.0f} : zero;
+                    if (n < 4) v = *reinterpret_cast<const f32x4*>(&S.g[80 + n][at]);
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[q], e1[q], acc1[t], 0, 0, 0);
@@ -453,9 +479,8 @@ __global__ __launch_bounds__(kBlock) void mlp_grad_kernel(const float* __restric
     for (int t = 0; t < 6; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int p = 16 * t + 4 * kq + q;
-            const int k = p < kEncRows ? enc_feature(p) : kMlpPE;
-            if (p <= kEncRows && (p == kEncRows || k < kMlpPE)) out[kP1 + k * kMlpH + j] = acc1[t][q];
+            const int k = 16 * t + 4 * kq + q;
+            if (k <= kMlpPE) out[kP1 + k * kMlpH + j] = acc1[t][q];
         }
 #pragma unroll
     for (int t = 0; t < 5; ++t)

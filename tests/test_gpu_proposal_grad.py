@@ -53,3 +53,10 @@ def test_batch_gradient_edges(n):
     assert np.all(np.abs(got[:mlp.N_PARAMS] - want) <= 2.0 ** -14 * mag + 1e-12)
     assert got[mlp.N_PARAMS] == 0.0
     assert abs(float(loss.item()) - want_loss) <= 1e-5 * want_loss
+    # parameters that are not 16-byte aligned: the same sums
+    shifted = torch.cat([torch.zeros(1, device=dev), Pd])[1:]
+    assert shifted.data_ptr() % 16 != 0
+    again = torch.zeros_like(grad)
+    _lib.mlp_loss_grad(shifted, Xd, Yd, again, loss, ws, idx=torch.from_numpy(idx).to(dev))
+    torch.cuda.synchronize()
+    assert torch.equal(again, grad)
