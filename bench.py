@@ -49,6 +49,12 @@ BYTES_SIGMA_WORDS = 8 * 16       # words holding coefficients 0..31 (F32 store)
 BYTES_LEAF = 42 * 16             # all 42 words of a leaf (F32 store)
 
 
+def render_direct(tree, cams, opts, **kw):
+    """fpo_render without its decode-first route: the paths timed here are the
+    per-segment IDFT (fourier) and renders of snapshots the bench bakes itself."""
+    return _lib.render(tree, cams, opts, decode=False, **kw)
+
+
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
@@ -182,7 +188,7 @@ def bake_leg(dev, sc, tree, oracle_mod, n_t: int = 64, reps: int = 5):
                 st.wait_stream(stream)
             for i, q in enumerate(range(0, n_t, per)):
                 with torch.cuda.stream(streams[i % n_streams]):
-                    _lib.render(tree, cams[q:q + per], opts_q[i], rgb=frames[q:q + per])
+                    render_direct(tree, cams[q:q + per], opts_q[i], rgb=frames[q:q + per])
             for st in streams[1:]:
                 stream.wait_stream(st)
 
@@ -265,7 +271,7 @@ def per_frame_leg(dev, sc, tree, oracle_mod, n_frames: int = 60, reps: int = 3, 
             for f in frame_ids:
                 # the cameras of frame f read snapshot f: offset the store by f records of leaf_stride
                 o_f = _lib.make_opts(stop_T=sc.stop_T, snapshot=store[f], snapshot_dtype=dt)
-                _lib.render(tree, cams_all[f * per:(f + 1) * per], o_f, rgb=frames)
+                render_direct(tree, cams_all[f * per:(f + 1) * per], o_f, rgb=frames)
         run()
         torch.cuda.synchronize()
         a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -281,7 +287,7 @@ def per_frame_leg(dev, sc, tree, oracle_mod, n_frames: int = 60, reps: int = 3, 
         if oracle_mod is not None:
             f = frame_ids[-1]
             o_f = _lib.make_opts(stop_T=sc.stop_T, snapshot=store[f], snapshot_dtype=dt)
-            _lib.render(tree, cams_all[f * per:(f + 1) * per], o_f, rgb=frames)
+            render_direct(tree, cams_all[f * per:(f + 1) * per], o_f, rgb=frames)
             rng = np.random.default_rng(60)
             ci = rng.integers(0, per, oracle_rays); py = rng.integers(0, H, oracle_rays)
             px = rng.integers(0, W, oracle_rays)
@@ -308,7 +314,7 @@ def per_frame_leg(dev, sc, tree, oracle_mod, n_frames: int = 60, reps: int = 3, 
         _lib.bake_times(tree, b10, _lib.FPO_F32, out=snap)
         for q, f in enumerate(frame_ids):
             o_f = _lib.make_opts(stop_T=sc.stop_T, snapshot=snap[q], snapshot_dtype=_lib.FPO_F32)
-            _lib.render(tree, cams_all[f * per:(f + 1) * per], o_f, rgb=frames)
+            render_direct(tree, cams_all[f * per:(f + 1) * per], o_f, rgb=frames)
     decode()
     torch.cuda.synchronize()
     a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -482,7 +488,7 @@ def convergence_leg(dev, dijk, gt, init, cams, n_steps: int = 3000, every: int =
                               train_times[(7 * k + 2) % len(train_times)]) for k in range(n_eval)]
     gt_tree = _lib.DeviceTree.from_leaves(dijk, gt, 8, device=dev)
     opts = _lib.make_opts(stop_T=1e-3)
-    want_held, _ = _lib.render(gt_tree, held, opts)
+    want_held, _ = render_direct(gt_tree, held, opts)
     del gt_tree
     out = {}
     for lr in (1e-2, 1e-3):
@@ -492,7 +498,7 @@ def convergence_leg(dev, dijk, gt, init, cams, n_steps: int = 3000, every: int =
         train_cams = [cams[i] for i in tr_idx]
 
         def psnr(view_cams, want):
-            got, _ = _lib.render(ft.tree, view_cams, opts)
+            got, _ = render_direct(ft.tree, view_cams, opts)
             mse = float(((got - want) ** 2).mean())
             return round(10 * np.log10(1.0 / mse), 3) if mse > 0 else float("inf")
         curve = [{"step": 0, "seconds": 0.0, "psnr_train_views_db": psnr(train_cams, want_train),
@@ -646,7 +652,7 @@ def _proposal_scene(dev, sc, tree, oracle_mod, n_train, train_steps, batch, orac
                           coarse_bits=bits, proposal=packed, workspace=ws)
             if decode:
                 kw.update(snapshot=snap, snapshot_dtype=_lib.FPO_F32)
-            _lib.render(rt, cams[j * per:(j + 1) * per], _lib.make_opts(stop_T=sc.stop_T, **kw), rgb=frames)
+            render_direct(rt, cams[j * per:(j + 1) * per], _lib.make_opts(stop_T=sc.stop_T, **kw), rgb=frames)
             if sample:
                 sel = np.nonzero((ci >= j * per) & (ci < (j + 1) * per))[0]
                 if len(sel):
@@ -890,12 +896,12 @@ def layouts_leg(dev, sc, tree, reps: int = 3):
 
         def fourier():
             for j in js:
-                _lib.render(vt, cams[j * per:(j + 1) * per], opts_f, rgb=frames)
+                render_direct(vt, cams[j * per:(j + 1) * per], opts_f, rgb=frames)
 
         def decode():
             for q, j in enumerate(js):
                 _lib.bake_times(vt, basis[q:q + 1], _lib.FPO_F32, out=snap)
-                _lib.render(vt, cams[j * per:(j + 1) * per], opts_s, rgb=frames)
+                render_direct(vt, cams[j * per:(j + 1) * per], opts_s, rgb=frames)
 
         def idft():
             for q in range(len(js)):
@@ -910,7 +916,7 @@ def layouts_leg(dev, sc, tree, reps: int = 3):
         # quantised stores of the layout: codes (+ one F32 scale per leaf) and the Fourier-mode render from them
         for dt, name in ((_lib.FPO_BF16, "bf16"), (_lib.FPO_FP8_E4M3, "fp8")):
             qt = _lib.quantize(vt, dt)
-            q_ms = timed(lambda: [_lib.render(qt, cams[j * per:(j + 1) * per], opts_f, rgb=frames) for j in js])
+            q_ms = timed(lambda: [render_direct(qt, cams[j * per:(j + 1) * per], opts_f, rgb=frames) for j in js])
             row[f"store_GB_{name}"] = round(L * (nc * (2 if dt == _lib.FPO_BF16 else 1) + 4) / 1e9, 3)
             row[f"fourier_{name}_ms_per_launch"] = round(q_ms, 3)
             row[f"fourier_{name}_fps_1080p"] = round(per / (q_ms * 1e-3), 1)
@@ -1074,7 +1080,7 @@ def main():
                     if ev_r is not None:
                         ev_r[j][0].record(st)
                     tr = pruned_trees[j] if mode == "decode_pruned" else union_tree if decode else tree
-                    _lib.render(tr, cams[j * per:(j + 1) * per], opts_s[j] if decode else opts_f,
+                    render_direct(tr, cams[j * per:(j + 1) * per], opts_s[j] if decode else opts_f,
                                 rgb=frames[j * per:(j + 1) * per])
                     if ev_r is not None:
                         ev_r[j][1].record(st)

@@ -435,12 +435,13 @@ def pack_coeffs(src, perm, n_leaves: int, leaf_stride: int, dst, layout: Optiona
                                  None if layout is None else ctypes.byref(layout), _t_ptr(dst), _stream()))
 
 
-def render(tree: DeviceTree, cams, opts: Optional[RenderOpts] = None, rgb=None, T=None, want_T: bool = False):
+def render(tree: DeviceTree, cams, opts: Optional[RenderOpts] = None, rgb=None, T=None, want_T: bool = False,
+           decode: bool = True):
     """fpo_render -> (rgb [n][H][W][3], T [n][H][W] or None).  Views of
     coefficients that are large against the tree go through fpo_render_decoded
     with a workspace for the call (at most 4 GiB, from torch's allocator), but
-    not while a HIP graph is captured (it would keep the workspace) and not if
-    the workspace cannot be had."""
+    not while a HIP graph is captured (it would keep the workspace), not if
+    the workspace cannot be had, and not with decode=False."""
     import torch
     opts = opts or make_opts()
     n, H, W = len(cams), int(cams[0].height), int(cams[0].width)
@@ -451,7 +452,7 @@ def render(tree: DeviceTree, cams, opts: Optional[RenderOpts] = None, rgb=None, 
         T = torch.empty((n, H, W), dtype=torch.float32, device=dev)
     tv = tree.view()
     arr = camera_struct(cams)
-    nbytes = lib().fpo_render_decode_bytes(ctypes.byref(tv), arr, n, ctypes.byref(opts))
+    nbytes = lib().fpo_render_decode_bytes(ctypes.byref(tv), arr, n, ctypes.byref(opts)) if decode else 0
     if nbytes > 0 and not torch.cuda.is_current_stream_capturing():
         try:
             ws = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
