@@ -53,6 +53,7 @@ struct CamLaunch {
     int32_t W, H, bx_per_cam, blocks_per_cam, n_cams;
     int32_t cbx_per_cam, crows_per_cam;     // camera kernel tiles (cam_tile_w x cam_tile_h of the mode)
     int32_t group_rows;              // tile rows per XCD group (xcd_row)
+    int32_t mix_cams;                // rows of all cameras in turn (cam_row)
     uint32_t snap_bytes;             // BUF kernels: bytes of one camera's snapshot records
     float bg[3];
     float stop_T;
@@ -77,8 +78,8 @@ __device__ inline int xcd_band(int bid, int nblocks)
     return (bid & 7) * per + (bid >> 3);
 }
 
-// Camera kernels: block index -> tile row of the launch (the rows of all
-// cameras, one camera after another) and column bx.  The rows go out in groups
+// Camera kernels: block index -> tile row of the launch, counted in the order
+// of cam_row, and column bx.  The rows go out in groups
 // of group_rows, eight groups at a time, one per XCD; the XCDs' order turns by
 // one from one eight to the next.  render_impl chooses the group.
 __device__ inline int xcd_row(int bid, int bx_per_row, int group_rows, int& bx)
@@ -88,6 +89,27 @@ __device__ inline int xcd_row(int bid, int bx_per_row, int group_rows, int& bx)
     bx = j - r * bx_per_row;
     const int k = r / group_rows;
     return (8 * k + (((bid & 7) + k) & 7)) * group_rows + (r - k * group_rows);
+}
+
+// Row `row` of the launch, in the order it goes out: camera ci and tile row by;
+// false past the last.  Each camera's rows go from its middle outwards (middle,
+// one above, one below, ...), or with mix_cams all cameras' middle rows first:
+// a wave through the scene takes a fifth of a launch, so these start early and
+// the empty rows at the edge fill the time they need at the end.
+__device__ inline bool cam_row(int row, const CamLaunch& a, int& ci, int& by)
+{
+    int i;
+    if (a.mix_cams) {
+        i = row / a.n_cams;
+        ci = row - i * a.n_cams;
+        if (i >= a.crows_per_cam) return false;
+    } else {
+        ci = row / a.crows_per_cam;
+        i = row - ci * a.crows_per_cam;
+        if (ci >= a.n_cams) return false;
+    }
+    by = (a.crows_per_cam - 1) / 2 + ((i & 1) ? (i + 1) / 2 : -(i / 2));
+    return true;
 }
 
 // Skip pre-pass: per pixel, a part of the chord [t_start, t_end] outside
@@ -223,11 +245,8 @@ __global__ __launch_bounds__(64 * WAVES, BUF && PARTS == 1 ? 32 / WAVES : 1) voi
     constexpr int kTileW = cam_tile_w(WAVES, PARTS);
     constexpr int kTileH = cam_tile_h(WAVES, PARTS);
     __shared__ int s_stack[kStackLevels * kThreads];
-    int bx;
-    const int row = xcd_row(blockIdx.x, a.cbx_per_cam, a.group_rows, bx);
-    const int ci = row / a.crows_per_cam;
-    if (ci >= a.n_cams) return;
-    const int by = row - ci * a.crows_per_cam;
+    int bx, ci, by;
+    if (!cam_row(xcd_row(blockIdx.x, a.cbx_per_cam, a.group_rows, bx), a, ci, by)) return;
     const int wv = threadIdx.x >> 6;
     const int ln = threadIdx.x & 63;
     const int part = ln / kPix;               // which part of the chord this lane walks
@@ -623,15 +642,20 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
         a.Tout = T_out ? T_out + (int64_t)c0 * W * H : nullptr;
         const int64_t total = (int64_t)nc * a.blocks_per_cam;
         const int64_t crows = (int64_t)nc * a.crows_per_cam;
-        // Groups of tile rows per XCD.  With a multiple of 8 cameras each XCD
-        // takes whole cameras: equal work, and neighbouring rays share one L2.
-        // Otherwise single rows in turn, which leaves the rows through the
-        // scene's middle to no XCD in particular.  2 M leaves at 1080p: one
-        // camera from Fourier coefficients 2.80 ms in bands of rows and 1.40 ms
-        // in single rows, from a pruned snapshot 0.79 and 0.60 ms, four cameras
-        // 3.88 and 3.50 ms; 16 cameras 12.58 and 12.95 ms.  Groups of two or
-        // more rows were never better than single ones.
-        a.group_rows = nc % 8 == 0 ? (int)((crows + 7) / 8) : 1;
+        // Which tiles an XCD takes.  Where the cameras read the same records,
+        // single rows in turn, all cameras' middle rows first.  Cameras with
+        // records of their own go one after another, a multiple of 8 as bands of
+        // rows (whole cameras per XCD), others in single rows.  2 M leaves at
+        // 1080p, bands of rows / single rows in order / as chosen: 16 cameras of
+        // one pruned snapshot (ten launches and their bake) 29.9 / 30.2 / 28.4 ms,
+        // 12 cameras - / 2.52 / 2.24 ms a launch, four 1.00 / 1.03 / 0.88, one
+        // 0.79 / 0.60 / 0.60; 16 cameras of 16 snapshots with their decode 4.84 /
+        // 4.97 / 4.80 ms, five (500x500, depth 8) - / 0.52 / 0.50.  Bands leave the
+        // rows through the scene's middle to a few XCDs and the longest rays to
+        // the end.
+        a.mix_cams = 1;
+        for (int i = 1; i < nc; ++i) a.mix_cams = a.mix_cams && a.cam[i].snap == a.cam[0].snap;
+        a.group_rows = !a.mix_cams && nc % 8 == 0 ? (int)((crows + 7) / 8) : 1;
         const int64_t groups = (crows + a.group_rows - 1) / a.group_rows;
         const int64_t ctotal = (groups + 7) / 8 * 8 * a.group_rows * a.cbx_per_cam;
         if (ctotal > INT32_MAX - 8) return fail(FPO_E_INVALID, "launch too large");
