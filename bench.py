@@ -52,6 +52,7 @@ BYTES_LEAF = 42 * 16             # all 42 words of a leaf (F32 store)
 def render_direct(tree, cams, opts, **kw):
     """fpo_render without its decode-first route: the paths timed here are the
     per-segment IDFT (fourier) and renders of snapshots the bench bakes itself."""
+    from paper_2202_08614_amd import _lib
     return _lib.render(tree, cams, opts, decode=False, **kw)
 
 
