@@ -52,7 +52,9 @@ class FPORender(torch.autograd.Function):
 def render(tree: _lib.DeviceTree, o, d, t_idx, basis, opts: Optional[_lib.RenderOpts] = None):
     """Colours [n][3] of rays (o, d) at basis rows t_idx, differentiable in
     tree.coeffs."""
-    return FPORender.apply(tree.coeffs, tree, o, d, t_idx, basis, opts or _lib.make_opts())
+    # without gradients the forward keeps no records
+    coeffs = tree.coeffs if torch.is_grad_enabled() else tree.coeffs.detach()
+    return FPORender.apply(coeffs, tree, o, d, t_idx, basis, opts or _lib.make_opts())
 
 
 class Adam:

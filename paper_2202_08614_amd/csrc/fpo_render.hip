@@ -329,7 +329,7 @@ struct RaysLaunch {
     float* Tout;
     float bg[3];
     float stop_T;
-    int32_t* rec_count;     // segment records (one ray per wave only): per-ray count, -1 on overflow
+    int32_t* rec_count;     // segment records (render_rays_record_kernel): per-ray count, -1 on overflow
     float4* rec;            // [n][rec_cap] records of 32 bytes
     int32_t rec_cap;
 };

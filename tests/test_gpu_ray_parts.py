@@ -150,6 +150,9 @@ def test_autograd_and_batched_backward_equal_the_direct_call(dev, n):
     (second,) = torch.autograd.grad(out, tree.coeffs, g)
     torch.cuda.synchronize()
     assert moved and torch.equal(out.detach(), rgb)
+    with torch.no_grad():
+        quiet = autograd.render(tree, *rays, basis, opts)
+    assert not quiet.requires_grad and torch.equal(quiet, rgb)
     top = float(direct.abs().max())
     for other in (batched, first, second, hooked):
         assert float((other - direct).abs().max()) <= 1e-4 * top
