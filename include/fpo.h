@@ -610,16 +610,14 @@ fpo_status fpo_fusion_observe(const fpo_tree_view* tree, const float* values, co
 fpo_status fpo_fusion_apply(float* values, float* weight, int32_t* count, float* acc, int64_t n_leaves,
                             void* stream);
 
-/* fpo_fusion_observe and fpo_fusion_apply of one view in one call (Sec. 3, Eq.
- * 3-5): the same update up to FP32 rounding and the order of the sums,
- * including what earlier observe calls left in acc, which is zero afterwards.
- * Observations are collected per leaf in `workspace` instead of being added to
- * acc; if they do not fit, the view is taken through acc.
+/* fpo_fusion_observe, then fpo_fusion_apply, of one view (Sec. 3, Eq. 3-5): what
+ * earlier observe calls left in acc is part of the update, and acc is zero
+ * afterwards.
  *   values, weight, count  device, as for fpo_fusion_apply (all n_leaves).
- *   workspace  device, 256-byte aligned; needs no initialisation.  Written by
- *              the call's device work; calls in flight at once need one each.
- * fpo_fusion_view_bytes: a workspace that holds the observations of a view of
- * this size (at most about 2.5 GiB), or 0 where it would be larger.  No device
+ *   workspace  device, 256-byte aligned; its size is checked, its contents are
+ *              neither read nor written.
+ * fpo_fusion_view_bytes: a workspace that the call takes for a view of this
+ * size, or 0 for images above its limit (then use the two calls).  No device
  * work. */
 int64_t fpo_fusion_view_bytes(const fpo_tree_view* tree, const fpo_camera* cam);
 fpo_status fpo_fusion_view(const fpo_tree_view* tree, float* values, float* weight, int32_t* count,

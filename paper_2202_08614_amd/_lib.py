@@ -817,26 +817,9 @@ def fusion_apply(values, weight, count, acc, n_leaves: int):
 
 
 def fusion_view(tree: DeviceTree, values, weight, count, cam, field, acc, tau: float = 1e-3):
-    """fpo_fusion_view with a workspace for the call (from torch's allocator);
-    fusion_observe and fusion_apply where that is too large, cannot be had, or
-    would be kept by a HIP graph under capture."""
-    import torch
-    tv = tree.view()
-    cs = camera_struct([cam])
-    fs = field_struct(field) if not isinstance(field, FieldC) else field
-    nbytes = lib().fpo_fusion_view_bytes(ctypes.byref(tv), cs)
-    ws = None
-    if nbytes > 0 and not torch.cuda.is_current_stream_capturing():
-        try:
-            ws = torch.empty((nbytes,), dtype=torch.uint8, device=values.device)
-        except torch.OutOfMemoryError:
-            ws = None
-    if ws is None:
-        fusion_observe(tree, values, cam, fs, acc, tau)
-        fusion_apply(values, weight, count, acc, tree.n_leaves)
-        return
-    _check(lib().fpo_fusion_view(ctypes.byref(tv), _t_ptr(values), _t_ptr(weight), _t_ptr(count), cs,
-                                 ctypes.byref(fs), float(tau), _t_ptr(acc), _t_ptr(ws), nbytes, _stream()))
+    """One view: fusion_observe, then fusion_apply."""
+    fusion_observe(tree, values, cam, field, acc, tau)
+    fusion_apply(values, weight, count, acc, tree.n_leaves)
 
 
 # ---------------------------------------------------------------------------

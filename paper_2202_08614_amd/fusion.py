@@ -4,8 +4,7 @@ A static PlenOctree (leaf records [leaf_stride][32]: sigma, then z_{c,j} at
 1 + 9c + j) is fused with observations of a radiance field from many views,
 one view after another: fpo_fusion_observe walks every pixel ray with the
 current values and accumulates the observations per leaf, fpo_fusion_apply
-updates every observed leaf once (Eq. 3-5) and clears the accumulators;
-fpo_fusion_view does both.
+updates every observed leaf once (Eq. 3-5) and clears the accumulators.
 """
 from __future__ import annotations
 
@@ -33,7 +32,8 @@ class Fusion:
 
     def view(self, cam) -> None:
         """Fuse one view: observe with the current values, then update."""
-        _lib.fusion_view(self.tree, self.values, self.weight, self.count, cam, self.field, self.acc, self.tau)
+        _lib.fusion_observe(self.tree, self.values, cam, self.field, self.acc, self.tau)
+        _lib.fusion_apply(self.values, self.weight, self.count, self.acc, self.tree.n_leaves)
 
     def run(self, cams: Sequence) -> None:
         for cam in cams:
