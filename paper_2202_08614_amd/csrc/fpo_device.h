@@ -236,13 +236,18 @@ struct NoStop {
 // PART: report only the segments whose entry lies in [t_start, t_end).  The
 // walk starts by descending to the slot around t_start and takes that slot's
 // own entry time (the last of its lower planes) as t_cur.  Every entry time is
-// then a plane's crossing time by the same expression (p - x) k as in a walk
-// from 0, so that of the parts of a chord exactly one reports each segment,
-// also where the descent at t_start rounds into a neighbouring slot.
+// then a plane's crossing time by the same expression (p - x) k, and the
+// descents go by these times too: the slot found at t_cur is the one whose
+// lower planes are crossed by then and whose upper planes are not.  So all
+// parts of a chord walk the same slots, and exactly one reports each segment.
+// (A point x + t d can round onto a plane long before (p - x) k where the ray
+// runs along it: a part that descended by points started behind slots that it
+// owned.)
 template <bool TWO = false, int STRIDE = kBlock, bool PART = false, class Visitor, class Stop>
 __device__ inline void walk(const TreeDev& T, const Ray& r, int* stk, Visitor& vis, float t_end, Stop& stop,
                             float t_start = 0.0f)
 {
+    if (PART && !(t_start < t_end)) return;
     // The child table is read through a buffer resource: 32-bit byte offsets
     // (no 64-bit address arithmetic per step), and a read past the table
     // returns 0 (an empty slot).
@@ -297,8 +302,17 @@ __device__ inline void walk(const TreeDev& T, const Ray& r, int* stk, Visitor& v
                 const float top = __builtin_ldexpf(1.0f, csh) - 1.0f;
                 const float tg = t_cur * fG;
 #pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    q[a] = (int)__builtin_amdgcn_fmed3f(fmaf(tg, fabsf(r.d[a]), xf[a]), pos[a], pos[a] + top);
+                for (int a = 0; a < 3; ++a) {
+                    float c = __builtin_amdgcn_fmed3f(fmaf(tg, fabsf(r.d[a]), xf[a]), pos[a], pos[a] + top);
+                    if constexpr (PART) {
+                        // the point is off by roundings: at most one cell
+                        c = floorf(c);
+                        const float lower = (c - xf[a]) * k[a], upper = (c + 1.0f - xf[a]) * k[a];
+                        c += lower > t_cur ? -1.0f : upper <= t_cur ? 1.0f : 0.0f;
+                        c = __builtin_amdgcn_fmed3f(c, pos[a], pos[a] + top);
+                    }
+                    q[a] = (int)c;
+                }
             }
             do {
                 stk[csh * STRIDE] = no;    // the node and the child the ray is in
