@@ -52,11 +52,14 @@ struct CamLaunch {
     const uint32_t* bits;            // coarse occupancy (suffix checks)
     int32_t W, H, bx_per_cam, blocks_per_cam, n_cams;
     int32_t cbx_per_cam, crows_per_cam;     // camera kernel tiles (cam_tile_w x cam_tile_h of the mode)
-    int32_t group_rows;              // tile rows per XCD group (xcd_row)
-    int32_t mix_cams;                // rows of all cameras in turn (cam_row)
     uint32_t snap_bytes;             // BUF kernels: bytes of one camera's snapshot records
     float bg[3];
     float stop_T;
+    // Last: with these two in front of snap_bytes the compiler took 120 instead
+    // of 94 registers for the F32 coefficient kernels and up to 140 for the other
+    // layouts (4 and 3 waves per SIMD instead of 5).
+    int32_t group_rows;              // tile rows per XCD group (xcd_row)
+    int32_t mix_cams;                // rows of all cameras in turn (cam_row)
 };
 static_assert(sizeof(CamLaunch) <= 4096, "kernel argument block too large");
 
