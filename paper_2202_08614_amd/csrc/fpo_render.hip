@@ -522,21 +522,79 @@ static int mode_of(const fpo_tree_view* t, const fpo_render_opts* o)
 
 using namespace fpo;
 
-// Lanes per ray of a camera launch over `pixels` pixels.  Parts shorten the
-// longest rays, which a launch that does not fill the machine waits for, but
-// cost work (a part's lanes idle where their stretch is empty, and parts behind
-// the ray's end are dropped); the longer the rays, in lattice cells, the later
-// the work wins.  Measured at depths 7 (60 k leaves) / 9 (2 M leaves), one part
-// against the chosen number, in us: F32 snapshot 200x200 117 / 627 -> 42 / 110
-// (16 parts), 400x400 106 / 572 -> 69 (8) / 143 (16), 640x640 107 / 532 -> 109 /
-// 255 (8), 1920x1080 123 / 555 -> 241 / 495 (8), two of them 183 / 692 -> 485 /
-// 973 (8); F32 coefficients 400x400 187 / 973 -> 136 / 433 (16), 640x640 214 /
-// 1077 -> 307 / 708 (16); BF16 coefficients 400x400 167 / 827 -> 174 / 413 (16),
-// 640x640 184 / 885 -> 399 / 872 (16).  The limits double per level between.
-static int ray_parts(int mode, int max_depth, int64_t pixels)
+// Share of an image inside the rectangle around the projection of the box
+// [lo, hi] (the leaves' bounds): 0 where the box is out of view, 1 where it
+// reaches the eye's plane.  fr as camera_frame gives it.
+static double seen_share(const float fr[12], const float* lo, const float* hi)
 {
-    if (mode >= 16) return pixels <= (512ll << max_depth) ? 16 : pixels <= (4096ll << max_depth) ? 8 : 1;
-    return pixels <= ((mode == FPO_F32 ? 1536ll : 1024ll) << max_depth) ? 16 : 1;
+    double x[2] = {1.0, -1.0}, y[2] = {1.0, -1.0};        // least and greatest, in half images
+    int ahead = 0;
+    for (int c = 0; c < 8; ++c) {
+        double f = 0.0, r = 0.0, u = 0.0, rr = 0.0, uu = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double v = (double)((c >> a) & 1 ? hi[a] : lo[a]) - fr[a];
+            f += v * fr[3 + a];
+            r += v * fr[6 + a];
+            u += v * fr[9 + a];
+            rr += (double)fr[6 + a] * fr[6 + a];
+            uu += (double)fr[9 + a] * fr[9 + a];
+        }
+        if (f < 1e-3) continue;
+        ++ahead;
+        x[0] = std::min(x[0], r / (rr * f));
+        x[1] = std::max(x[1], r / (rr * f));
+        y[0] = std::min(y[0], u / (uu * f));
+        y[1] = std::max(y[1], u / (uu * f));
+    }
+    if (ahead == 0) return 0.0;
+    if (ahead < 8) return 1.0;
+    const double w = std::min(x[1], 1.0) - std::max(x[0], -1.0), h = std::min(y[1], 1.0) - std::max(y[0], -1.0);
+    return w > 0.0 && h > 0.0 ? 0.25 * w * h : 0.0;
+}
+
+// Pixels of a launch: all, and those that see the leaves' bounds, from outside
+// the box of twice their size and from inside it.
+struct LaunchPixels {
+    double all, far, near;
+};
+
+static void count_view(LaunchPixels& n, const float fr[12], double pixels, const float* lo, const float* hi)
+{
+    bool near = true;
+    for (int a = 0; a < 3; ++a) near = near && std::fabs(fr[a] - 0.5f * (lo[a] + hi[a])) <= hi[a] - lo[a];
+    n.all += pixels;
+    (near ? n.near : n.far) += pixels * seen_share(fr, lo, hi);
+}
+
+// Lanes per ray of a camera launch.  Parts shorten the longest rays, which a
+// launch that does not fill the machine waits for, but cost work: a part's lanes
+// idle where their stretch is empty, and the parts behind a ray's end are walked
+// for nothing.  So they pay while few pixels see the scene, fewer from nearby or
+// inside, where rays end early, and the longer the rays, in lattice cells, the
+// more: the limits double per level.  us at depth 7 (60 k leaves) / 9 (2 M), one
+// lane against 8 or 16, 40 degrees of view from 1.6, 0.8 and 0.15 cubes off the
+// middle:
+//   F32 snapshot 200x200   144 / 773 -> 39 / 133 (16), 130 / 696 -> 51 / 138 (16),
+//                           87 / 444 -> 79 / 254 (16)
+//     400x400              136 / 688 -> 66 / 149 (8, 16), 121 / 658 -> 91 / 241
+//                          (8, 16), 87 / 461 -> 167 / 642 (8: not taken)
+//     1920x1080            - / 690 -> 421 (8), - / 715 -> 1058 (8: not taken), - /
+//                          1516 -> 4847 (8: not taken)
+//   F32 coefficients 400x400  203 / 1020 -> 84 / 311 (16), 204 / 1078 -> 211 / 604
+//                          (16, at depth 7 not taken), 159 / 852 -> 503 / 1694 (not taken)
+//   BF16 200x200           181 / 823 -> 57 / 180 (16), 171 / 932 -> 95 / 270 (16),
+//                          122 / 620 -> 171 / 659 (not taken)
+//   FP8 200x200            293 / 1135 -> 81 / 239 (16), 276 / 1134 -> 123 / 299
+//                          (16), 191 / 873 -> 251 / 808 (at depth 7 not taken)
+static int ray_parts(int mode, int max_depth, const LaunchPixels& n)
+{
+    const auto within = [&](double all, double far, double near) {
+        const double scale = std::ldexp(1.0, -max_depth);
+        return n.all * scale <= all && n.far * scale / far + n.near * scale / near <= 1.0;
+    };
+    if (mode >= 16) return within(512, 512, 128) ? 16 : within(4096, 1024, 256) ? 8 : 1;
+    if (mode == FPO_F32) return within(1536, 512, 160) ? 16 : 1;
+    return within(1024, 300, mode == FPO_BF16 ? 64 : 96) ? 16 : 1;
 }
 
 template <int MODE, bool BUF = false>
@@ -605,11 +663,13 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
     static thread_local dev::CamLaunch a;
     static thread_local dev::SkipLaunch sk;
     std::memset(&a, 0, sizeof(a));
+    a.tree = tree_dev(tree);
+    LaunchPixels seen{0.0, 0.0, 0.0};
     for (int i = 0; i < n_cams; ++i) {
         float fr[12];
         if ((st = camera_frame(cams[i], fr)) != FPO_OK) return st;
+        if (i < per_launch) count_view(seen, fr, (double)W * H, a.tree.box_lo, a.tree.box_hi);
     }
-    a.tree = tree_dev(tree);
     a.W = W;
     a.H = H;
     a.bx_per_cam = (W + 15) / 16;
@@ -617,7 +677,7 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
     for (int c = 0; c < 3; ++c) a.bg[c] = opts->bg[c];
     a.stop_T = opts->stop_T;
     const int mode = mode_of(tree, opts);
-    const int parts = variant || skip ? 1 : ray_parts(mode, tree->max_depth, (int64_t)std::min(n_cams, per_launch) * W * H);
+    const int parts = variant || skip ? 1 : ray_parts(mode, tree->max_depth, seen);   // by the first launch
     {
         const int waves = variant ? dev::cam_waves(tree->dtype) : dev::cam_waves(mode);
         const int tw = dev::cam_tile_w(waves, parts), th = dev::cam_tile_h(waves, parts);
@@ -655,10 +715,12 @@ static fpo_status render_impl(const fpo_tree_view* tree, const fpo_camera* cams,
         // 0.79 / 0.60 / 0.60; 16 cameras of 16 snapshots with their decode 4.84 /
         // 4.97 / 4.80 ms, five (500x500, depth 8) - / 0.52 / 0.50.  Bands leave the
         // rows through the scene's middle to a few XCDs and the longest rays to
-        // the end.
+        // the end; views from near, whose rows are all alike, gain from neighbours
+        // in one L2 (800x800 inside the 2 M leaves 730 us in rows, 705 in bands).
         a.mix_cams = 1;
         for (int i = 1; i < nc; ++i) a.mix_cams = a.mix_cams && a.cam[i].snap == a.cam[0].snap;
-        a.group_rows = !a.mix_cams && nc % 8 == 0 ? (int)((crows + 7) / 8) : 1;
+        const bool bands = (!a.mix_cams && nc % 8 == 0) || seen.near > seen.far;
+        a.group_rows = bands ? (int)((crows + 7) / 8) : 1;
         const int64_t groups = (crows + a.group_rows - 1) / a.group_rows;
         const int64_t ctotal = (groups + 7) / 8 * 8 * a.group_rows * a.cbx_per_cam;
         if (ctotal > INT32_MAX - 8) return fail(FPO_E_INVALID, "launch too large");
@@ -763,10 +825,14 @@ extern "C" int64_t fpo_render_decode_bytes(const fpo_tree_view* tree, const fpo_
 {
     if (check_tree(tree, true) != FPO_OK || check_opts(opts, tree, true) != FPO_OK) return 0;
     if (opts->snapshot || opts->flags != 0 || !cams || n_cams < 1) return 0;
-    for (int i = 0; i < n_cams; ++i)
-        if (!std::isfinite(cams[i].time) || cams[i].width != cams[0].width || cams[i].height != cams[0].height ||
-            cams[i].width < 1 || cams[i].height < 1)
+    const dev::TreeDev td = dev::tree_dev(tree);
+    double px = 0.0;              // of the images that the leaves' bounds are in
+    for (int i = 0; i < n_cams; ++i) {
+        float fr[12];
+        if (cams[i].width != cams[0].width || cams[i].height != cams[0].height || camera_frame(cams[i], fr) != FPO_OK)
             return 0;
+        if (seen_share(fr, td.box_lo, td.box_hi) > 0.0) px += (double)cams[i].width * cams[i].height;
+    }
     const int64_t rec = tree->n_leaves * 128;
     if ((kDecodeMaxBytes - kDecodeHead) / rec < 1) return 0;
     const int cap = (int)std::min<int64_t>((kDecodeMaxBytes - kDecodeHead) / rec, dev::kDecodeTimes);
@@ -784,8 +850,8 @@ extern "C" int64_t fpo_render_decode_bytes(const fpo_tree_view* tree, const fpo_
     // 9.4 ms for 16 views of 1920x1080 (33 Mpixel; 12.6 ms from F32
     // coefficients, 3.2 ms from decoded records), 930 us for one, 640 us at
     // 800x800, 290 us at 400x400; at depth 8 (300 k leaves) 240 us at 800x800,
-    // at depth 7 (60 k leaves) 130 us at 800x800 and 67 us at 400x400.
-    const double px = (double)n_cams * cams[0].width * cams[0].height;
+    // at depth 7 (60 k leaves) 130 us at 800x800 and 67 us at 400x400.  A view
+    // that the scene is not in is rendered in 20 us either way.
     const double saved = std::ldexp(2.85e-4 * px + 4e-4 * std::min(px, 1048576.0), tree->max_depth - 9);
     const double bytes = (double)tree->n_leaves * 16 * record_words(tree->dtype, FPO_N_SIGMA, FPO_N_SH_FOURIER) * groups +
                          (double)rec * decoded;
