@@ -988,18 +988,19 @@ extern "C" fpo_status fpo_render_noalloc(const fpo_tree_view* tree, const fpo_ca
 }
 
 // Lanes per ray of a batch of n rays (see ray_parts; batch rays seldom miss the
-// scene, and share no leaves).  Measured from F32 coefficients at depths 7 (100 k
-// leaves) / 9 (2 M), in us for 32, 16 and 1 lanes: 3001 rays 31 39 152 / 62 97
-// 513, 8192 rays 52 55 197 / 81 123 602, 60 k rays - 239 254 / - 413 879, 120 k
-// rays - 449 299 / - 741 1002; from F32 snapshots 5000 rays 23 30 108 / 45 70
-// 304, 60 k rays 139 87 157 / 174 148 519, 250 k rays 519 292 194 / 651 499 671.
-// One ray per wave, which served up to 32768 rays from F32 coefficients before,
-// took 74 / 220 us for 3001 rays and 100 / 241 us for 8192.
+// scene, and share no leaves).  us for 32, 16 and 1 lanes, rays from outside
+// through the middle, at depths 7 (60 k leaves) / 9 (2 M): F32 coefficients 4000
+// rays 39 55 203 / 89 151 703, 16,000 rays 108 103 197 / 229 286 796, 64,000
+// rays 364 330 266 / 775 880 1051, 128,000 rays 707 626 331 / 1490 1677 1271;
+// BF16 64,000 rays 338 296 242 / 708 758 953, 128,000 rays 654 547 270 / 1364
+// 1419 1016; F32 snapshots 16,000 rays 63 46 127 / 115 124 522, 64,000 rays 192
+// 121 155 / 341 277 612, 128,000 rays 363 212 175 / 640 481 649, 256,000 rays
+// 713 396 217 / 1241 890 727.
 static int batch_parts(int mode, int max_depth, int64_t n)
 {
     if (mode == FPO_F32 && n <= FPO_RECORD_MAX_RAYS) return record_parts(max_depth, n);
     if (n <= (64ll << max_depth)) return 32;
-    return n <= ((mode >= 16 ? 768ll : 384ll) << max_depth) ? 16 : 1;
+    return n <= ((mode >= 16 ? 320ll : 200ll) << max_depth) ? 16 : 1;
 }
 
 template <int MODE>
