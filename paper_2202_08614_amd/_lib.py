@@ -256,15 +256,18 @@ def with_records(opts: "RenderOpts", workspace) -> "RenderOpts":
 
 def spare_record_workspace(tree: "DeviceTree", opts: "RenderOpts", n_rays: int, device):
     """A record workspace for a call that was not asked for records but runs
-    faster with them (F32 coefficients, at most RECORD_MAX_RAYS rays), of at
-    most 64 MiB; None where records do not apply, cannot be had, or would be
-    kept by a HIP graph under capture."""
+    faster with them (F32 coefficients, at most RECORD_MAX_RAYS rays): up to 256
+    records a ray (rays with more are walked again), in at most 64 MiB, or the
+    size of the coefficients (the gradient takes as much) up to 256 MiB; None
+    where records do not apply, cannot be had, or would be kept by a HIP graph
+    under capture."""
     import torch
     if (opts.flags != 0 or opts.snapshot or tree.dtype != FPO_F32 or not 0 < n_rays <= RECORD_MAX_RAYS
             or torch.cuda.is_current_stream_capturing()):
         return None
+    most = max(64 << 20, min(256 << 20, tree.coeffs.numel() * tree.coeffs.element_size()))
     try:
-        return record_workspace(n_rays, min(128, (64 << 20) // (RECORD_BYTES * n_rays)), device)
+        return record_workspace(n_rays, min(256, most // (RECORD_BYTES * n_rays)), device)
     except torch.OutOfMemoryError:
         return None
 
