@@ -354,11 +354,13 @@ fpo_status fpo_trace_rays(const fpo_tree_view* tree, const float* o, const float
 /* Gradient of a loss L w.r.t. the leaf coefficients, through the render of
  * fpo_render_rays (Sec. 4.3: the IDFT is differentiable, so the photometric
  * loss of Eq. 13 back-propagates into the Fourier coefficients).  Without
- * FPO_RAYS_RECORD each ray's walk and shading are recomputed by one wave.
- * With it (opts->workspace as the forward left it, for the same rays, tree
- * values and opts), 8 waves share each ray's recorded segments, one wave per
- * segment, and only rays whose records overflowed are walked again; the
- * gradient is the same up to the order of the atomic additions.
+ * FPO_RAYS_RECORD each ray is walked and shaded again: up to 24 << max_depth
+ * rays in the parts that a recording forward cuts them into, more rays one by
+ * one.  With it (opts->workspace as the forward left it, for the same rays,
+ * tree values and opts), eight rows of 16 lanes share each ray's recorded
+ * segments, and only rays whose records overflowed are walked again.  Where the
+ * rays are cut alike the gradient is the same up to the order of the atomic
+ * additions, otherwise up to FP32 rounding.
  *   o, d, t_idx, basis, n_t, n_rays, opts: as passed to fpo_render_rays
  *            (opts->snapshot must be NULL; the store must be FPO_F32).
  *   rgb_fwd  device [n_rays][3], the forward colours of these rays.

@@ -932,5 +932,113 @@ struct RowGrad {
     }
 };
 
+// --------------------------------------------------------------------------
+// The backward of large batches that kept no records: one ray per wave, all
+// lanes walking it (uniform branches, broadcast child loads), the 166
+// coefficients of a leaf spread over the 64 lanes.  One pass reads each record
+// and scatters its gradient, where RowGrad needs the walk's own reads before.
+// --------------------------------------------------------------------------
+
+// This lane's coefficient slots for one ray: q = lane + 64 s, s < 3.  A
+// density slot (q < 31) weighs b_q; an SH slot q = 31 + (9 c + j) 5 + i
+// weighs Y_j b_i and feeds channel c.
+struct WaveSlots {
+    float w[3];
+    int c[3];        // channel of an SH slot, -1 density, -2 past the 166 coefficients
+    __device__ inline void init(int lane, const float* brow, const float* Y)
+    {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const int q = lane + kWave * s;
+            if (q >= FPO_N_COEFF) {
+                w[s] = 0.0f;
+                c[s] = -2;
+            } else if (q < FPO_N_SIGMA) {
+                w[s] = brow[q];
+                c[s] = -1;
+            } else {
+                const int u = q - FPO_N_SIGMA;
+                const int ch = u / (FPO_N_SH * FPO_N_SH_FOURIER);
+                const int rem = u - ch * (FPO_N_SH * FPO_N_SH_FOURIER);
+                const int j = rem / FPO_N_SH_FOURIER;
+                const int i = rem - j * FPO_N_SH_FOURIER;
+                float yj = Y[0];
+#pragma unroll
+                for (int jj = 1; jj < FPO_N_SH; ++jj) yj = j == jj ? Y[jj] : yj;
+                w[s] = yj * brow[i];
+                c[s] = ch;
+            }
+        }
+    }
+};
+
+// As RowGrad, along the walk.
+struct WaveGrad {
+    const TreeDev& T;
+    WaveSlots sl;
+    int lane;
+    float Tr;
+    float C[3];
+    float stop_T;
+    float Cf[3];
+    float g[3];
+    float* grad;          // F32 leaf records, 192 floats per slot
+    float pk[3];          // this lane's coefficients of the leaf being shaded
+
+    // All three before the density sum decides whether the colour is needed:
+    // one memory round trip per segment instead of two.
+    __device__ inline void prefetch(int leaf)
+    {
+        constexpr int kRecFloats = 4 * Pack<FPO_F32>::R;
+        const float* rc = reinterpret_cast<const float*>(T.recs) + (int64_t)leaf * kRecFloats + lane;
+        pk[0] = rc[0];
+        pk[1] = rc[kWave];
+        pk[2] = sl.c[2] >= 0 ? rc[2 * kWave] : 0.0f;
+    }
+
+    __device__ inline bool segment(int leaf, float t0, float t1)
+    {
+        constexpr int kRecFloats = 4 * Pack<FPO_F32>::R;
+        const float delta = t1 - t0;
+        const float k[3] = {pk[0], pk[1], pk[2]};
+        const float sraw = wave_sum(sl.c[0] == -1 ? sl.w[0] * k[0] : 0.0f);
+        const float sig = T.sigma_scale * fmaxf(sraw, 0.0f);
+        if (!(sig * delta > 0.0f)) return false;   // transparent: contributes nothing
+        float h[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) h[ch] = fmaf(sl.c[s] == ch ? sl.w[s] : 0.0f, k[s], h[ch]);
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) h[ch] = wave_sum(h[ch]);
+        const float e = __expf(-sig * delta);
+        const float w = Tr * (1.0f - e);
+        Tr *= e;
+        float dsig = 0.0f, dh[3];
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            const float col = sigmoidf_(h[ch]);
+            C[ch] = fmaf(w, col, C[ch]);
+            dsig = fmaf(g[ch], Tr * col - (Cf[ch] - C[ch]), dsig);
+            dh[ch] = g[ch] * w * col * (1.0f - col);
+        }
+        dsig *= delta * T.sigma_scale;    // sigma_raw > 0 here
+        float* gr = grad + (int64_t)leaf * kRecFloats + lane;
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const int ch = sl.c[s];
+            if (ch == -2) continue;
+            const float dv = ch == -1 ? dsig : ch == 0 ? dh[0] : ch == 1 ? dh[1] : dh[2];
+            unsafeAtomicAdd(gr + kWave * s, dv * sl.w[s]);
+        }
+        return Tr < stop_T;
+    }
+};
+
+__device__ inline void prefetch_leaf(WaveGrad& v, int leaf)
+{
+    v.prefetch(leaf);
+}
+
 }  // namespace dev
 }  // namespace fpo

@@ -2,19 +2,20 @@
 // render into the leaf Fourier coefficients, the L2 photometric loss of
 // Eq. 13 and a fused Adam update over the coefficient planes.
 //
-// Backward: each segment of positive optical depth is taken on its own, as the
-// forward recorded it (FPO_RAYS_RECORD) or as walking the ray again gives it; besides the records, the only forward state used is the ray's
-// final colour.  Walking
-// front to back with transmittance T_i and accumulated colour A_i, the
-// suffix R_i = C - A_i gives
+// Backward: each segment of positive optical depth is taken as the forward
+// recorded it (FPO_RAYS_RECORD) or as walking the ray again gives it; besides the
+// records, the only forward state used is the ray's final colour.  Walking front
+// to back with transmittance T_i and accumulated colour A_i, the suffix R_i =
+// C - A_i gives
 //     dL/dsigma_i = delta_i * sum_c g_c (T_{i+1} c_{i,c} - R_{i,c}),
 //     dL/dh_{i,c} = g_c T_i alpha_i c_{i,c} (1 - c_{i,c}),
 // and through Eq. 7 / Eq. 9 and the SH basis of Eq. 1
 //     dL/dk^sigma_q     = s [sigma_raw > 0] dL/dsigma_i b_q,
 //     dL/dk^z_{c,j,i}   = dL/dh_{i,c} Y_j b_i.
-// 16 lanes per segment: each lane owns up to eleven of a leaf's 166
-// coefficients, so every sample's gradients go out as FP32 atomic adds over 64
-// consecutive bytes each, into records laid out like the F32 coefficient store.
+// 16 lanes per segment (64 where a wave walks a ray): each lane owns up to
+// eleven (three) of a leaf's 166 coefficients, so every sample's gradients go out
+// as FP32 atomic adds over 64 (256) consecutive bytes each, into records laid out
+// like the F32 coefficient store.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -148,6 +149,35 @@ __global__ __launch_bounds__(kWave) void render_backward_walk_kernel(BackwardLau
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
+}
+
+// The backward without records, one ray per wave.
+__global__ __launch_bounds__(kBlock) void render_backward_wave_kernel(BackwardLaunch a)
+{
+    __shared__ int s_stack[kStackLevels * kBlock];
+    const int64_t r_id = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    if (r_id >= a.n) return;
+    WaveGrad sh{a.tree};
+    sh.lane = threadIdx.x & (kWave - 1);
+    sh.Tr = 1.0f;
+    sh.stop_T = a.stop_T;
+    sh.grad = a.grad;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        sh.C[c] = 0.0f;
+        sh.Cf[c] = a.rgb_fwd[r_id * 3 + c];
+        sh.g[c] = a.grad_rgb[r_id * 3 + c];
+    }
+    if (sh.g[0] == 0.0f && sh.g[1] == 0.0f && sh.g[2] == 0.0f) return;
+    Ray r;
+    if (!setup_ray_in(a.tree.box_lo, a.tree.box_hi, a.o[3 * r_id], a.o[3 * r_id + 1], a.o[3 * r_id + 2],
+                   a.d[3 * r_id], a.d[3 * r_id + 1], a.d[3 * r_id + 2], r))
+        return;
+    const int ti = min(max(a.t_idx[r_id], 0), a.n_t - 1);
+    float Y[FPO_N_SH];
+    sh9(r.d[0], r.d[1], r.d[2], Y);
+    sh.sl.init(sh.lane, a.basis + (int64_t)ti * FPO_BASIS_STRIDE, Y);
+    walk<true>(a.tree, r, s_stack + threadIdx.x, sh);
 }
 
 // The backward from segment records: row (r, q) takes ray r's recorded
@@ -373,6 +403,17 @@ extern "C" fpo_status fpo_render_backward(const fpo_tree_view* tree, const float
         const int64_t rgrid = (n_rays * dev::kRecGroups + dev::kBlock / dev::kRow - 1) / (dev::kBlock / dev::kRow);
         hipLaunchKernelGGL(dev::render_backward_rec_kernel, dim3((unsigned)rgrid), dim3(dev::kBlock), 0, s, a);
         if ((st = launch_status("fpo_render_backward")) != FPO_OK) return st;
+    }
+    // Cutting rays into parts pays while one wave per ray leaves the machine
+    // waiting for long rays.  us for parts / one wave per ray, rays through the
+    // leaves: depth 6 (20 k leaves) 1000 rays 29 / 45, 3000 41 / 50, 16,384 141 /
+    // 116; depth 7 (120 k) 3000 rays 101 / 119, 8192 212 / 165, 100,000 2035 /
+    // 1342; depth 8 (300 k) 3000 rays 120 / 183, 8192 228 / 218, 32,768 954 / 757;
+    // depth 9 (2 M) 3000 rays 230 / 355, 8192 486 / 465, 32,768 2406 / 1481.
+    if (opts->flags != FPO_RAYS_RECORD && n_rays > (24ll << tree->max_depth)) {
+        const int64_t wgrid = (n_rays + dev::kBlock / dev::kWave - 1) / (dev::kBlock / dev::kWave);
+        hipLaunchKernelGGL(dev::render_backward_wave_kernel, dim3((unsigned)wgrid), dim3(dev::kBlock), 0, s, a);
+        return launch_status("fpo_render_backward");
     }
     // every ray, or those whose records overflowed
     const int parts = record_parts(tree->max_depth, n_rays);
