@@ -1000,7 +1000,8 @@ static int batch_parts(int mode, int max_depth, int64_t n)
 {
     if (mode == FPO_F32 && n <= FPO_RECORD_MAX_RAYS) return record_parts(max_depth, n);
     if (n <= (64ll << max_depth)) return 32;
-    return n <= ((mode >= 16 ? 320ll : 200ll) << max_depth) ? 16 : 1;
+    return n <= (mode >= 16 ? std::min<int64_t>(320ll << max_depth, 163840) : std::min<int64_t>(200ll << max_depth, 81920))
+               ? 16 : 1;
 }
 
 template <int MODE>
