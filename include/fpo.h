@@ -354,7 +354,7 @@ fpo_status fpo_trace_rays(const fpo_tree_view* tree, const float* o, const float
 /* Gradient of a loss L w.r.t. the leaf coefficients, through the render of
  * fpo_render_rays (Sec. 4.3: the IDFT is differentiable, so the photometric
  * loss of Eq. 13 back-propagates into the Fourier coefficients).  Without
- * FPO_RAYS_RECORD each ray is walked and shaded again: up to 24 << max_depth
+ * FPO_RAYS_RECORD each ray is walked and shaded again: up to 32 << max_depth
  * rays in the parts that a recording forward cuts them into, more rays one by
  * one.  With it (opts->workspace as the forward left it, for the same rays,
  * tree values and opts), eight rows of 16 lanes share each ray's recorded

@@ -536,7 +536,7 @@ def render_backward(tree: DeviceTree, o, d, t_idx, basis, rgb_fwd, grad_rgb, gra
     """fpo_render_backward: adds dL/dk into grad_coeffs (F32 leaf records).
     Without records, RECORD_MAX_RAYS rays and less give the gradient that a
     recorded forward gives, up to the order of the atomic sums: where the call
-    itself would not cut the rays as the forward does (more than 24 << depth
+    itself would not cut the rays as the forward does (more than 32 << depth
     rays), by a forward that records and a backward over its records.  That
     takes 0.7 to 1.4 times what walking the rays takes (32768 rays at depth 9
     706 instead of 785 us for 2 M leaves seen by cameras; at depth 7, 120 k
@@ -551,7 +551,7 @@ def render_backward(tree: DeviceTree, o, d, t_idx, basis, rgb_fwd, grad_rgb, gra
                                          n_t, n, ctypes.byref(op), _t_ptr(rgb_fwd), _t_ptr(grad_rgb),
                                          _t_ptr(grad_coeffs), _stream()))
     ws = None
-    if (24 << tree.max_depth) < n <= RECORD_MAX_RAYS:
+    if (32 << tree.max_depth) < n <= RECORD_MAX_RAYS:
         ws = spare_record_workspace(tree, opts, n, o.device)
     if ws is None:
         call(opts)

@@ -409,8 +409,11 @@ extern "C" fpo_status fpo_render_backward(const fpo_tree_view* tree, const float
     // leaves: depth 6 (20 k leaves) 1000 rays 29 / 45, 3000 41 / 50, 16,384 141 /
     // 116; depth 7 (120 k) 3000 rays 101 / 119, 8192 212 / 165, 100,000 2035 /
     // 1342; depth 8 (300 k) 3000 rays 120 / 183, 8192 228 / 218, 32,768 954 / 757;
-    // depth 9 (2 M) 3000 rays 230 / 355, 8192 486 / 465, 32,768 2406 / 1481.
-    if (opts->flags != FPO_RAYS_RECORD && n_rays > (24ll << tree->max_depth)) {
+    // depth 9 (2 M) 3000 rays 230 / 355, 16,384 882 / 834, 32,768 2406 / 1481; from
+    // cameras, most of whose rays pass beside the leaves, 8192 at depth 8 113 /
+    // 188, 16,384 at depth 9 363 / 488.  The line is where the recorded forward
+    // goes from 32 to 16 parts, too (record_parts).
+    if (opts->flags != FPO_RAYS_RECORD && n_rays > (32ll << tree->max_depth)) {
         const int64_t wgrid = (n_rays + dev::kBlock / dev::kWave - 1) / (dev::kBlock / dev::kWave);
         hipLaunchKernelGGL(dev::render_backward_wave_kernel, dim3((unsigned)wgrid), dim3(dev::kBlock), 0, s, a);
         return launch_status("fpo_render_backward");

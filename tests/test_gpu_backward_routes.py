@@ -1,4 +1,4 @@
-"""fpo_render_backward without records: up to 24 << depth rays in parts, more
+"""fpo_render_backward without records: up to 32 << depth rays in parts, more
 with one wave per ray.  Either side of the limit, and past the largest recorded
 batch, the gradient is the recorded one up to FP32 rounding: transmittances of
 some 30 factors in other orders (30 x 2^-24 each way, in sums over many rays)
@@ -28,7 +28,7 @@ def _backward(tree, rays, basis, rgb, g, out, opts):
 
 
 @pytest.mark.parametrize("stop_T", [0.0, 1e-2])
-@pytest.mark.parametrize("n", [1, 63, 24 << DEPTH, (24 << DEPTH) + 1, 2047, 32768, 32771])
+@pytest.mark.parametrize("n", [1, 63, 32 << DEPTH, (32 << DEPTH) + 1, 2047, 32768, 32771])
 def test_walked_gradient_equals_the_recorded_one(dev, n, stop_T):
     import torch
     dijk = synth.random_tree_leaves(23, DEPTH, p_split=0.8)
