@@ -182,9 +182,13 @@ def _t_ptr(t):
 
 def _stream():
     """The current stream's handle, without the Stream object that
-    torch.cuda.current_stream() builds for it (3 us of a call)."""
+    torch.cuda.current_stream() builds for it (3 us of a call) where torch has
+    the call that it makes."""
     import torch
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(raw(torch.cuda.current_device()))
 
 
 def make_layout(period: float = 60.0, sigma_scale: float = 64.0, n_sigma: int = N_SIGMA,
