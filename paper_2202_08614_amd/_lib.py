@@ -9,6 +9,7 @@ raises: there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 from typing import Optional, Sequence
 
@@ -258,6 +259,23 @@ def with_records(opts: "RenderOpts", workspace) -> "RenderOpts":
     return o
 
 
+def _scratch(tree: "DeviceTree", nbytes: int, alloc):
+    """alloc(): nbytes of device memory that a call runs faster with, or None
+    where it cannot be had.  torch waits for the GPU and empties its cache before
+    it gives up; the tree's next 64 calls that want as much don't ask."""
+    import torch
+    if nbytes >= tree.refused_bytes:
+        tree.refused_calls -= 1
+        if tree.refused_calls <= 0:
+            tree.refused_bytes = math.inf
+        return None
+    try:
+        return alloc()
+    except torch.OutOfMemoryError:
+        tree.refused_bytes, tree.refused_calls = nbytes, 64
+        return None
+
+
 def spare_record_workspace(tree: "DeviceTree", opts: "RenderOpts", n_rays: int, device):
     """A record workspace for a call that was not asked for records but runs
     faster with them (F32 coefficients, at most RECORD_MAX_RAYS rays): up to 256
@@ -266,14 +284,12 @@ def spare_record_workspace(tree: "DeviceTree", opts: "RenderOpts", n_rays: int, 
     where records do not apply, cannot be had, or would be kept by a HIP graph
     under capture."""
     import torch
-    if (opts.flags != 0 or opts.snapshot or tree.dtype != FPO_F32 or not 0 < n_rays <= RECORD_MAX_RAYS
-            or torch.cuda.is_current_stream_capturing()):
+    if (opts.flags != 0 or opts.snapshot or tree.dtype != FPO_F32 or tree.coeffs is None
+            or not 0 < n_rays <= RECORD_MAX_RAYS or torch.cuda.is_current_stream_capturing()):
         return None
     most = max(64 << 20, min(256 << 20, tree.coeffs.numel() * tree.coeffs.element_size()))
-    try:
-        return record_workspace(n_rays, min(256, most // (RECORD_BYTES * n_rays)), device)
-    except torch.OutOfMemoryError:
-        return None
+    cap = min(256, most // (RECORD_BYTES * n_rays))
+    return _scratch(tree, RECORD_BYTES * n_rays * cap, lambda: record_workspace(n_rays, cap, device))
 
 
 def record_counts(workspace, n_rays: int):
@@ -350,6 +366,9 @@ class DeviceTree:
         self.leaf_stride = int(leaf_stride)
         self.perm = perm
         self.layout = layout
+        # scratch of this size could not be had, and calls that go without it (_scratch)
+        self.refused_bytes = math.inf
+        self.refused_calls = 0
 
     @classmethod
     def from_leaves(cls, leaf_dijk: np.ndarray, coeffs: np.ndarray, max_depth: int,
@@ -463,10 +482,7 @@ def render(tree: DeviceTree, cams, opts: Optional[RenderOpts] = None, rgb=None, 
     arr = camera_struct(cams)
     nbytes = lib().fpo_render_decode_bytes(ctypes.byref(tv), arr, n, ctypes.byref(opts)) if decode else 0
     if nbytes > 0 and not torch.cuda.is_current_stream_capturing():
-        try:
-            ws = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
-        except torch.OutOfMemoryError:
-            ws = None
+        ws = _scratch(tree, nbytes, lambda: torch.empty((nbytes,), dtype=torch.uint8, device=dev))
         if ws is not None:
             _check(lib().fpo_render_decoded(ctypes.byref(tv), arr, n, ctypes.byref(opts), _t_ptr(rgb), _t_ptr(T),
                                             _t_ptr(ws), nbytes, _stream()))
