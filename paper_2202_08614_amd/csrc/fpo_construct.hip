@@ -7,18 +7,15 @@
 // produces, so that the DFT of T records sampled at t = 0 .. T-1 is the exact
 // inverse of fpo_bake_times for band-limited leaves.
 //
-// DFT kernel.  A 256-thread block takes 64 leaves; its wave g covers one
-// quarter of each leaf's outputs (g = 0: the 31 density coefficients; g = 1..3:
-// nine SH coefficients x 5 Fourier terms), so every wave runs one uniform code
-// path.  The weighted basis c_i IDFT_i(t) of all frames sits in LDS (c_0 = 1/T,
-// c_i = 2/T, or 1/T for every i with the printed weights), computed from exact
-// integer phases (i t mod 2T) with sinpi / cospi.  The 64 records of a tile are
-// contiguous in every frame: the block stages 4 frames of them at a time into
-// LDS with whole-line loads, then each wave reads its values from there; the
-// next 4 frames' loads are in flight in registers meanwhile.  The kernel
-// streams T records per leaf and is bound by HBM reads.
+// DFT kernel.  8 lanes take a leaf, a lane one 16-byte word of its record in every
+// frame, and sum the terms of that word's values and a share of the density's 31
+// (dft_kernel).  The weighted basis c_i IDFT_i(t) of all frames sits in LDS
+// (c_0 = 1/T, c_i = 2/T, or 1/T for every i with the printed weights), computed
+// from exact integer phases (i t mod 2T) with sinpi / cospi.  The kernel streams
+// T records per leaf and is bound by HBM.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>

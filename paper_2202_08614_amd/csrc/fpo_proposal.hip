@@ -120,9 +120,7 @@ __global__ __launch_bounds__(kBlock) void labels_kernel(LabelLaunch a)
 // ---------------------------------------------------------------------------
 // FP32 training kernels
 // ---------------------------------------------------------------------------
-constexpr int kRows = 344;               // workspace floats per ray (fpo_mlp_workspace_floats)
 constexpr int kChunk = 64;               // rays a block takes at a time
-constexpr int kSplit = 1024;             // workspace: rays per further FPO_MLP_N_PARAMS_PADDED floats
 constexpr int kGradBlocks = 256;         // one block (136 KB of LDS) per CU
 constexpr int kParamsPad = FPO_MLP_N_PARAMS_PADDED;
 constexpr float kQIn = 0.1f;
@@ -140,18 +138,10 @@ __device__ inline void encode_f32(const float* x, float* g)
         }
 }
 
-// Forward pass of one ray in FP32.  Keeps a1 (needed by layer 2) and the
-// ReLU masks of both hidden layers.
-struct Fwd {
-    float a1[kMlpH];
-    float a2[kMlpH];
-    uint64_t m1, m2;
-    float o[3];
-};
-
-__device__ inline void forward_f32(const float* __restrict__ P, const float* g, Fwd& F)
+// Forward pass of one ray in FP32: the three outputs.
+__device__ inline void forward_f32(const float* __restrict__ P, const float* g, float* o)
 {
-    float z[kMlpH];
+    float z[kMlpH], a[kMlpH];
 #pragma unroll
     for (int j = 0; j < kMlpH; ++j) z[j] = P[kP1 + kMlpPE * kMlpH + j];
 #pragma unroll
@@ -160,32 +150,22 @@ __device__ inline void forward_f32(const float* __restrict__ P, const float* g, 
 #pragma unroll
         for (int j = 0; j < kMlpH; ++j) z[j] = fmaf(gk, P[kP1 + k * kMlpH + j], z[j]);
     }
-    F.m1 = 0;
 #pragma unroll
     for (int j = 0; j < kMlpH; ++j) {
-        F.a1[j] = fmaxf(z[j], 0.0f);
-        F.m1 |= (uint64_t)(z[j] > 0.0f) << j;
+        a[j] = fmaxf(z[j], 0.0f);
+        z[j] = P[kP2 + kMlpH * kMlpH + j];
     }
-#pragma unroll
-    for (int j = 0; j < kMlpH; ++j) z[j] = P[kP2 + kMlpH * kMlpH + j];
 #pragma unroll
     for (int k = 0; k < kMlpH; ++k) {
-        const float ak = F.a1[k];
 #pragma unroll
-        for (int j = 0; j < kMlpH; ++j) z[j] = fmaf(ak, P[kP2 + k * kMlpH + j], z[j]);
-    }
-    F.m2 = 0;
-#pragma unroll
-    for (int j = 0; j < kMlpH; ++j) {
-        F.a2[j] = fmaxf(z[j], 0.0f);
-        F.m2 |= (uint64_t)(z[j] > 0.0f) << j;
+        for (int j = 0; j < kMlpH; ++j) z[j] = fmaf(a[k], P[kP2 + k * kMlpH + j], z[j]);
     }
 #pragma unroll
-    for (int e = 0; e < 3; ++e) F.o[e] = P[kP3 + kMlpH * 3 + e];
+    for (int e = 0; e < 3; ++e) o[e] = P[kP3 + kMlpH * 3 + e];
 #pragma unroll
     for (int k = 0; k < kMlpH; ++k)
 #pragma unroll
-        for (int e = 0; e < 3; ++e) F.o[e] = fmaf(F.a2[k], P[kP3 + k * 3 + e], F.o[e]);
+        for (int e = 0; e < 3; ++e) o[e] = fmaf(fmaxf(z[k], 0.0f), P[kP3 + k * 3 + e], o[e]);
 }
 
 __global__ __launch_bounds__(kBlock) void mlp_forward_kernel(const float* __restrict__ P, const float* __restrict__ X,
@@ -193,14 +173,13 @@ __global__ __launch_bounds__(kBlock) void mlp_forward_kernel(const float* __rest
 {
     const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (r >= n) return;
-    float x[kMlpIn], g[kMlpPE];
+    float x[kMlpIn], g[kMlpPE], o[3];
 #pragma unroll
     for (int c = 0; c < kMlpIn; ++c) x[c] = X[r * kMlpIn + c];
     encode_f32(x, g);
-    Fwd F;
-    forward_f32(P, g, F);
+    forward_f32(P, g, o);
 #pragma unroll
-    for (int e = 0; e < 3; ++e) out[r * 3 + e] = F.o[e];
+    for (int e = 0; e < 3; ++e) out[r * 3 + e] = o[e];
 }
 
 __device__ inline float sigmoid_exact(float v) { return 1.0f / (1.0f + expf(-v)); }
@@ -585,13 +564,14 @@ __global__ __launch_bounds__(kBlock) void mlp_infer_kernel(const unsigned char* 
 using namespace fpo;
 
 static int64_t mlp_ld(int64_t n) { return (n + dev::kChunk - 1) / dev::kChunk * dev::kChunk; }
-static int64_t mlp_splits(int64_t n) { return (mlp_ld(n) + dev::kSplit - 1) / dev::kSplit; }
 
 extern "C" int64_t fpo_mlp_workspace_floats(int64_t n)
 {
     ApiRange api_range_("fpo_mlp_workspace_floats");
     if (n < 1) return 0;
-    return (int64_t)dev::kRows * mlp_ld(n) + mlp_splits(n) * dev::kParamsPad;
+    // fixed by the interface; the partial gradients take at most kGradBlocks *
+    // kParamsPad floats of it
+    return 344 * mlp_ld(n) + (mlp_ld(n) + 1023) / 1024 * dev::kParamsPad;
 }
 
 template <int MODE>
