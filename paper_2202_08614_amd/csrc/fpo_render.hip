@@ -592,6 +592,7 @@ static int ray_parts(int mode, int max_depth, const LaunchPixels& n)
         const double scale = std::ldexp(1.0, -max_depth);
         return n.all * scale <= all && n.far * scale / far + n.near * scale / near <= 1.0;
     };
+    if (n.far + n.near == 0.0) return 1;                 // nothing to walk
     if (mode >= 16) return within(512, 512, 128) ? 16 : within(4096, 1024, 256) ? 8 : 1;
     if (mode == FPO_F32) return within(1536, 512, 160) ? 16 : 1;
     return within(1024, 300, mode == FPO_BF16 ? 64 : 96) ? 16 : 1;
